@@ -532,7 +532,7 @@ def decode_cpu_baseline(spec, runner, q, n_c, seconds):
 
 # Sources whose kernels the committed traffic figure was measured on.
 TRAFFIC_SOURCES = {
-    "starkv_score": ["score_kernels.h", "score_slab.h", "score.hip", "score_bf16.hip",
+    "starkv_score": ["score_slab.h", "slab_grid.h", "score.hip", "score_bf16.hip",
                      "device_common.h"],
 }
 

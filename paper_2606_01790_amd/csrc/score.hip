@@ -1,9 +1,9 @@
 // Window attention scoring (sec. 3.3, Eqs. A_raw and base_score): launch
 // sequence, pooling and group aggregation.  The two MFMA passes and the
-// merge of their row statistics live in score_kernels.h.
+// merge of their row statistics live in score_slab.h.
 #include <algorithm>
 
-#include "score_kernels.h"
+#include "score_slab.h"
 
 namespace starkv {
 namespace {
@@ -73,6 +73,11 @@ int launch_score(const Geometry& g, const starkv_params& p, const void* q,
                  const void* k, const starkv_kv_layout& lay, float* S,
                  float* sbar, uint8_t* gstar, void* ws, void* stream) {
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  int dev = 0, n_cu = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      n_cu <= 0)
+    return (int)hipErrorInvalidDevice;
   const WsLayout wl = ws_layout(g);
   ScoreArgs a;
   a.q = q;
@@ -84,39 +89,27 @@ int launch_score(const Geometry& g, const starkv_params& p, const void* q,
   a.G = g.G;
   a.W = g.W;
   a.R = g.R;
-  a.Rpad = g.Rpad;
+  a.nrb = g.Rpad / 32;
   a.Lp = g.Lp;
   a.n_chunks_max = max_chunks(g);
-  // Each block scores one contiguous token range of one (layer, group).
-  // Up to 1024 blocks: two blocks per CU fit the LDS, so that is two full
-  // rounds over the 256 CUs; ranges are at least 256 tokens so that the
-  // window-query load stays a small fraction of the K traffic.
-  const long nlg = (long)g.n_layers * g.G;
-  long per_lg = 1024 / nlg;   // about two rounds of two blocks per CU
-  per_lg = std::min<long>(per_lg, (g.Lp + kMinChunk - 1) / kMinChunk);
-  per_lg = std::max<long>(per_lg, 1);
-  int chunk = (int)((g.Lp + per_lg - 1) / per_lg);
-  chunk = (chunk + 127) / 128 * 128;
-  a.chunk = chunk;
-  a.n_chunks = (g.Lp + chunk - 1) / chunk;
   a.scale = kLog2e / sqrtf((float)g.d);
   // per-head subspaces: head h of group g owns rows [h*W, (h+1)*W) of the
   // group's window rows, i.e. W/32 whole row blocks, or W/8 of the 8-row
-  // groups a wave keeps apart
-  a.Ns = g.Ns;
+  // groups a lane's rows fall into
   a.n_out = g.Ns / g.G;
-  if (a.n_out == 1) {
-    a.n_part = 1;
-    a.upo = g.Rpad / 32;
-  } else {
-    a.n_part = g.W % 32 == 0 ? 1 : 4;
-    a.upo = g.W / (32 / a.n_part);
-  }
+  a.upo = g.W % 32 == 0 ? g.W / 32 : g.W / 8;
   a.part = reinterpret_cast<float2*>(static_cast<char*>(ws) + wl.part_off);
   a.sraw = reinterpret_cast<float*>(static_cast<char*>(ws) + wl.sraw_off);
+  // pass 1 leaves one record per block and group (the workspace holds
+  // n_chunks_max); pass 2 may split finer, and shares slabs only where one
+  // sum per group is wanted
+  const int nlg = g.n_layers * g.G;
+  SlabLaunch p1, p2;
+  slab_launches(g.Lp, nlg, a.nrb, n_cu, a.n_chunks_max, a.n_out == 1,
+                a.n_out == 1 || a.W % 32 == 0, &p1, &p2);
 
-  const int err = g.dtype == STARKV_BF16 ? run_score_bf16(a, g.d, g.n_layers, st)
-                                         : run_score_f32(a, g.d, g.n_layers, st);
+  const int err = g.dtype == STARKV_BF16 ? run_score_bf16(a, g.d, p1, p2, st)
+                                         : run_score_f32(a, g.d, p1, p2, st);
   if (err) return err;
   const int radius = p.pool_kernel / 2;
   if (radius > kAggMaxRadius) return (int)hipErrorInvalidValue;   // validated before

@@ -1,121 +1,866 @@
-// Pass 2 of the window scoring (sec. 3.3, Eq. A_raw) for bf16 keys with
-// d = 128: for every past token t of a (layer, group), sum_r 2^(y_rt - c_r)
-// over the group's R window rows, with y = q.k * log2(e)/sqrt(d) and c_r the
-// row's log2-sum-exp from pass 1.  With one scoring subspace per KV group
-// the sum runs over all R rows; with per-head subspaces (PH), when each
-// head's W rows are whole 32-row blocks, over each head's own rows, one
-// output per head.
+// Window attention scoring (sec. 3.3): A_raw summed over the window rows of
+// each scoring subspace.
 //
-// Persistent design: one 512-thread block per CU walks a contiguous range
-// of the flattened (layer-group, 64-token slab) space.  For each group
-// segment of its range the block stages the group's window rows in LDS
-// (padded rows) together with c_r, merged once from the pass-1 chunk
-// statistics.  Each wave then takes whole slabs: it loads the slab's 64 K
-// rows straight from global memory into MFMA fragment registers (two
-// 32-token blocks), and for every 32-row block of the group it reads each Q
-// fragment once from LDS and feeds it to two v_mfma_f32_32x32x16_bf16, so
-// every token's sum over all R rows is completed inside one wave (no
-// cross-wave reduction, no barrier in the main loop).  The MFMAs of row
-// block rb+1 are interleaved with the exponentials of row block rb.
+// The window softmax of every query row needs that row's sum over all L_p
+// past keys before any key's normalised mass is known, so scoring runs in
+// two passes over K, with y = q.k * log2(e)/sqrt(d):
+//   pass 1  per (layer, group, block): for each window row r a reference
+//           M_r and the sum of 2^(y - M_r) over the block's tokens;
+//   pass 2  merges the blocks' statistics into c_r = M_r + log2(sum_r) and
+//           sums 2^(y_rt - c_r) over the rows of each subspace for every
+//           token t.
+//
+// Both passes are one persistent design.  A 512-thread block (one per CU)
+// takes a range of one or more (layer, group)'s 64-token slabs and stages
+// the group's R window rows in LDS (rows padded by 16 bytes: no bank
+// conflicts).  Each wave takes whole slabs: the slab's K rows go straight
+// from global memory into MFMA fragment registers, and the wave walks the
+// group's 32-row blocks, reading each Q fragment from LDS once for the
+// slab's two 32-token tiles.  No barrier inside the slab loop.
+//   - bf16: a slab's tiles form one sequence; the MFMAs of a tile are
+//     interleaved with the exponentials of the tile before it, two
+//     accumulator tiles in all.  The next slab's K is loaded behind the last
+//     tile's exponentials; the other wave of the SIMD covers its latency (a
+//     second register set for it, loaded a slab ahead, gained nothing).
+//   - The row-block loop is rolled (nothing per row block stays in
+//     registers), so one kernel serves every R.
+//   - What bounds it: power.  With normal random operands an MFMA loop alone
+//     runs at 1.74 PFLOP/s (1.70 GHz; 2.4 PFLOP/s and 2.4 GHz with zeros),
+//     with this epilogue at 1.30 and with the LDS reads at 1.23; the slab
+//     loop reaches 1.13 at 13,679 tokens of 28 layers.  A K load, a row per
+//     lane, takes 64 address cycles against 16 for contiguous lanes, about
+//     3.5 us for the first slabs of a block's eight waves.
+// Pass 1 puts tokens on the MFMA M axis: a lane owns one window row of the
+// tile and its reference is one register.  Pass 2 puts rows on M: a lane
+// owns one token and its sum over the rows completes in the wave.  Against
+// a pass 1 with K tiles in LDS and a wave per row block, one fragment read
+// per MFMA: 2209 -> 1772 us at 140,190 tokens and 14 row blocks, 130 -> 116
+// at 13,679 and 7, and 76 -> 69 at 8,297; fp32 at d = 64 with one row block
+// (there a block of one wave) 39 -> 23 us, and its pass 2 44 -> 22.
+//
+// fp32 keys run v_mfma_f32_32x32x2f32 (64 cycles per 2 k): the matrix core
+// bounds them, so their tiles are not interleaved.
 #pragma once
-#include "score_kernels.h"
+#include "device_common.h"
+#include "internal.h"
+#include "slab_grid.h"
 
 namespace starkv {
 
-struct SlabGrid {
-  int S;      // 64-token slabs per (layer, group)
-  int nlg;    // layers * groups
+struct ScoreArgs {
+  const void* q;
+  const void* k;
+  int64_t ls, gs, ts;   // element strides of the K cache
+  int H, G, W, R, nrb, Lp;
+  int n_chunks_max;
+  float scale;          // log2(e) / sqrt(d)
+  float2* part;         // [n_layers][G][n_chunks_max][nrb * 32]  (M, sum)
+  float* sraw;          // [n_layers][Ns][Lp]
+  // subspaces per KV group (1, or H/G per head), and the row blocks
+  // (kHeadBlocks) or 8-row groups (kHeadGroups) per head
+  int n_out, upo;
 };
 
 namespace {
 
-template <int NRB>
-struct SlabLds {
-  static constexpr int kQS = 136;                           // padded Q row (272 B)
-  static constexpr int kQBytes = NRB * 32 * kQS * 2;
-  static constexpr int kBytes = kQBytes + NRB * 32 * 4;     // + c_r
+constexpr int kSlabThreads = kSlabWaves * 64;
+constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kNegBig = -1e30f;
+// A block's sum against its reference stays below this unless a logit rises
+// 64 log2 units above the block's first slab; then the row statistics are
+// redone against exact running maxima.
+constexpr float kSumLimit = 18446744073709551616.0f;   // 2^64
+
+// Pass-2 output: one sum per group; one per head, a head being whole row
+// blocks; one per head, a head being whole 8-row groups.
+enum HeadLayout { kGroup = 0, kHeadBlocks = 1, kHeadGroups = 2 };
+
+// 16 bytes of a row: one bf16 MFMA step, or four fp32 ones.  Lane half h
+// supplies bytes 32 j + 16 h of its row in step j for both operands, so the
+// contraction pairs equal elements whatever order the hardware takes them.
+template <typename T>
+__device__ __forceinline__ f32x16 mma16(i32x4 a, i32x4 b, f32x16 c);
+template <>
+__device__ __forceinline__ f32x16 mma16<__bf16>(i32x4 a, i32x4 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+template <>
+__device__ __forceinline__ f32x16 mma16<float>(i32x4 a, i32x4 b, f32x16 c) {
+  const f32x4 fa = __builtin_bit_cast(f32x4, a), fb = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i], fb[i], c, 0, 0, 0);
+  return c;
+}
+
+template <typename T, int D>
+struct Shape {
+  static constexpr int kRowBytes = D * (int)sizeof(T);
+  static constexpr int kNP = kRowBytes / 32;        // 16-byte pieces per lane and row
+  static constexpr int kQStride = kRowBytes + 16;   // LDS bytes per window row
+  // 32-token tiles of a slab held at a time: 64 registers of K per set
+  static constexpr int kTB = kNP > 8 ? 1 : 2;
 };
+
+template <typename T, int D>
+using KFrags = i32x4[Shape<T, D>::kTB][Shape<T, D>::kNP];
+
+// The value lane l ^ 32 holds.  v_permlane32_swap exchanges the upper lane
+// half of its first operand with the lower half of its second, so with both
+// operands = v the first result holds the lower half's values in the upper
+// lanes and the second the upper half's values in the lower lanes.
+__device__ inline float other_half(float v, int half) {
+  const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(half ? sw[0] : sw[1]);
+}
+
+// The two waves of a SIMD take turns at the higher issue priority, slab by
+// slab: the older one would otherwise finish its slabs early and leave the
+// other to run alone at the end of the block.
+__device__ __forceinline__ void take_turn(int& turn) {
+  if ((turn ^= 1)) __builtin_amdgcn_s_setprio(0);
+  else __builtin_amdgcn_s_setprio(1);
+}
+
+// 2^((m - mn) * scale) for a running max m <= mn, ms = mn * scale.  Exactly 1
+// when the max did not move: with the -1e30 start value the fma would
+// otherwise return the rounding residual of the product, not 0.
+__device__ inline float rescale(float m, float mn, float ms, float scale) {
+  return m == mn ? 1.0f : __builtin_amdgcn_exp2f(fmaf(m, scale, -ms));
+}
+
+// Lanes 0-31: both halves of v0 added; lanes 32-63: both halves of v1.
+__device__ inline float add_halves(float v0, float v1) {
+  const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(v0), __float_as_uint(v1), false, false);
+  return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+}
 
 // Blocks are dealt to the 8 XCDs round-robin by id; the id is permuted so
 // that each XCD walks one contiguous part of the slab space (a bijection of
-// [0, gridDim.x)).
+// [0, gridDim.x), correct whatever the placement).
 __device__ inline int slab_block() {
   const int n = gridDim.x, b = blockIdx.x;
   const int xcd = b & 7, local = b >> 3, per = n >> 3, rem = n & 7;
   return xcd < rem ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
 }
 
-template <int NRB, bool PH>
-__global__ __launch_bounds__(512) void score_pass2_slab(ScoreArgs a, SlabGrid sg) {
-  using T = __bf16;
-  using M = Mfma<T>;
-  constexpr int NW = 8, TB = 2, SLAB = 64;
-  constexpr int QS = SlabLds<NRB>::kQS;
-  extern __shared__ __align__(16) unsigned char smem[];
-  T* qs = reinterpret_cast<T*>(smem);
-  float* cs = reinterpret_cast<float*>(smem + SlabLds<NRB>::kQBytes);
+// threadIdx.x, opaque to the compiler: what is computed from it stays where
+// it is written.  The slab loops need nearly every register, and thread
+// constants hoisted above them (staging indices, row offsets) end in
+// scratch memory, whose reloads wait for the K loads in flight.
+__device__ __forceinline__ int tid_here() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
 
-  const int nb = gridDim.x, b = slab_block();
-  const long total = (long)sg.S * sg.nlg;
-  const long lo = (long)b * total / nb, hi = (long)(b + 1) * total / nb;
+template <typename T, int D>
+__device__ inline const T* group_q(const ScoreArgs& a, int lg) {
+  const int layer = lg / a.G, g = lg - layer * a.G;
+  return reinterpret_cast<const T*>(a.q) +
+         ((size_t)layer * a.H + (size_t)g * (a.H / a.G)) * (size_t)a.W * D;
+}
+
+template <typename T>
+__device__ inline const T* group_k(const ScoreArgs& a, int lg) {
+  const int layer = lg / a.G, g = lg - layer * a.G;
+  return reinterpret_cast<const T*>(a.k) + (int64_t)layer * a.ls + (int64_t)g * a.gs;
+}
+
+// The group's window rows to LDS, rows R .. nrb * 32 zero.  The first batch
+// of 16-byte vectors is issued by q_issue; q_commit stores it and moves the
+// rest, so that a segment's other first loads can be issued between.
+constexpr int kQBatch = 7;
+template <typename T, int D>
+__device__ __forceinline__ void q_issue(const ScoreArgs& a, const T* qg, int i0,
+                                        i32x4 (&v)[kQBatch]) {
+  constexpr int VPR = Shape<T, D>::kRowBytes / 16;
+  const char* src = reinterpret_cast<const char*>(qg);
+#pragma unroll
+  for (int j = 0; j < kQBatch; ++j) {
+    const int i = min(i0 + j * kSlabThreads, a.R * VPR - 1);
+    v[j] = *reinterpret_cast<const i32x4*>(src + (size_t)i * 16);
+  }
+}
+template <typename T, int D>
+__device__ __forceinline__ void q_commit(const ScoreArgs& a, const T* qg, char* qs,
+                                         i32x4 (&v)[kQBatch]) {
+  using SH = Shape<T, D>;
+  constexpr int VPR = SH::kRowBytes / 16;
+  const int nv = a.nrb * 32 * VPR;
+  for (int i0 = tid_here();;) {
+#pragma unroll
+    for (int j = 0; j < kQBatch; ++j) {
+      const int i = i0 + j * kSlabThreads, row = i / VPR, part = i % VPR;
+      if (row >= a.R) v[j] = i32x4{0, 0, 0, 0};
+      if (i < nv) *reinterpret_cast<i32x4*>(qs + row * SH::kQStride + part * 16) = v[j];
+      __builtin_amdgcn_sched_barrier(0);   // one condition at a time
+    }
+    i0 += kQBatch * kSlabThreads;
+    if (i0 - (int)threadIdx.x >= nv) break;
+    q_issue<T, D>(a, qg, i0, v);
+  }
+}
+
+// One slab of K to LDS, rows as the window rows; vectors of this thread.
+template <typename T, int D>
+constexpr int slab_vecs() { return kSlab * (Shape<T, D>::kRowBytes / 16) / kSlabThreads; }
+template <typename T, int D>
+__device__ __forceinline__ void slab_issue(const ScoreArgs& a, const T* kg, int slab,
+                                           i32x4 (&v)[slab_vecs<T, D>()]) {
+  constexpr int VPR = Shape<T, D>::kRowBytes / 16;
+  const int tid = tid_here();
+  const int last = a.Lp - 1 - slab * kSlab;
+  const char* base = reinterpret_cast<const char*>(kg + (int64_t)slab * kSlab * a.ts);
+#pragma unroll
+  for (int j = 0; j < slab_vecs<T, D>(); ++j) {
+    const int i = tid + j * kSlabThreads, row = min(i / VPR, last), part = i % VPR;
+    v[j] = *reinterpret_cast<const i32x4*>(base + (int64_t)row * (a.ts * (int64_t)sizeof(T)) +
+                                           part * 16);
+  }
+}
+template <typename T, int D>
+__device__ __forceinline__ void slab_commit(char* ks, const i32x4 (&v)[slab_vecs<T, D>()]) {
+  using SH = Shape<T, D>;
+  constexpr int VPR = SH::kRowBytes / 16;
+  const int tid = tid_here();
+#pragma unroll
+  for (int j = 0; j < slab_vecs<T, D>(); ++j) {
+    const int i = tid + j * kSlabThreads, row = i / VPR, part = i % VPR;
+    *reinterpret_cast<i32x4*>(ks + row * SH::kQStride + part * 16) = v[j];
+  }
+}
+
+// K fragments of tiles cb0 .. cb0 + kTB - 1 of one slab: the token of row
+// l32 of each tile, this lane half's pieces.  Tokens past L_p re-read the
+// last one.
+template <typename T, int D>
+__device__ __forceinline__ void load_k(const ScoreArgs& a, const T* kg, int slab, int cb0,
+                                       KFrags<T, D>& kf) {
+  using SH = Shape<T, D>;
+  const int lane = tid_here() & 63, half = lane >> 5, l32 = lane & 31;
+  const char* base = reinterpret_cast<const char*>(kg + (int64_t)slab * kSlab * a.ts);
+  const int last = a.Lp - 1 - slab * kSlab;
+#pragma unroll
+  for (int cb = 0; cb < SH::kTB; ++cb) {
+    const int rel = min((cb0 + cb) * 32 + l32, last);
+    const char* row = base + (int64_t)rel * (a.ts * (int64_t)sizeof(T)) + half * 16;
+#pragma unroll
+    for (int j = 0; j < SH::kNP; ++j) kf[cb][j] = *reinterpret_cast<const i32x4*>(row + j * 32);
+  }
+}
+
+template <typename T, int D>
+__device__ __forceinline__ void load_q(const char* qrow, i32x4 (&qf)[Shape<T, D>::kNP]) {
+#pragma unroll
+  for (int j = 0; j < Shape<T, D>::kNP; ++j)
+    qf[j] = *reinterpret_cast<const i32x4*>(qrow + j * 32);
+}
+
+// One tile's MFMA chain.  TOK_M: tokens on the M axis (pass 1), else rows.
+template <typename T, int D, bool TOK_M>
+__device__ __forceinline__ f32x16 chain(const i32x4 (&qf)[Shape<T, D>::kNP],
+                                        const i32x4 (&kf)[Shape<T, D>::kNP]) {
+  f32x16 acc = {};
+#pragma unroll
+  for (int j = 0; j < Shape<T, D>::kNP; ++j)
+    acc = TOK_M ? mma16<T>(kf[j], qf[j], acc) : mma16<T>(qf[j], kf[j], acc);
+  return acc;
+}
+
+// Tokens on M: element e of this lane is token tb + 8 (e / 4) + 4 half + e % 4.
+__device__ __forceinline__ void mask_tokens(f32x16& acc, int tb, int Lp) {
+  const int left = Lp - tb - 4 * ((tid_here() & 63) >> 5);
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    if (8 * (e >> 2) + (e & 3) >= left) acc[e] = -INFINITY;
+    __builtin_amdgcn_sched_barrier(0);   // one condition at a time
+  }
+}
+
+// ---------------------------------------------------------------- stages
+// One tile's step of the bf16 sequence: the MFMAs of the next tile (nxt, K
+// fragments kf) interleaved with cur's 16 exponentials per lane.  RELOAD:
+// each Q fragment is replaced by the next row block's once it is used.
+// The order is pinned one MFMA at a time.  The exponentials start behind
+// the second MFMA: cur's own last MFMA, just before this step, has then
+// left the matrix core.
+// A tile's 16 values are added up in two chains of their own before they
+// join a longer sum.
+__device__ __forceinline__ void add_to(float& s, float v, bool first) { s = first ? v : s + v; }
+
+template <int NP>
+constexpr int stage_elem(int j) {   // cur's elements before step j
+  return j <= 1 ? 0 : (j - 1) * 16 / (NP - 1);
+}
+
+template <int D, bool RELOAD>
+__device__ __forceinline__ float stage1(i32x4 (&qf)[D / 16], const i32x4 (&kf)[D / 16],
+                                        const char* qnext, f32x16& nxt, const f32x16& cur,
+                                        float scale, float ms) {
+  constexpr int NP = D / 16;
+  float s[2];
+#pragma unroll
+  for (int j = 0; j < NP; ++j) {
+    nxt = mma16<__bf16>(kf[j], qf[j], j ? nxt : f32x16{});
+    if (RELOAD) qf[j] = *reinterpret_cast<const i32x4*>(qnext + j * 32);
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+      if (e >= stage_elem<NP>(j) && e < stage_elem<NP>(j + 1))
+        add_to(s[e & 1], __builtin_amdgcn_exp2f(fmaf(cur[e], scale, -ms)), e < 2);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  return s[0] + s[1];
+}
+
+template <int D, bool RELOAD>
+__device__ __forceinline__ float stage2(i32x4 (&qf)[D / 16], const i32x4 (&kf)[D / 16],
+                                        const char* qnext, f32x16& nxt, const f32x16& cur,
+                                        float scale, const float (&c)[16]) {
+  constexpr int NP = D / 16;
+  float s[2];
+#pragma unroll
+  for (int j = 0; j < NP; ++j) {
+    nxt = mma16<__bf16>(qf[j], kf[j], j ? nxt : f32x16{});
+    if (RELOAD) qf[j] = *reinterpret_cast<const i32x4*>(qnext + j * 32);
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+      if (e >= stage_elem<NP>(j) && e < stage_elem<NP>(j + 1))
+        add_to(s[e & 1], __builtin_amdgcn_exp2f(fmaf(cur[e], scale, -c[e])), e < 2);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  return s[0] + s[1];
+}
+
+// The same sums with no MFMAs to interleave.
+__device__ __forceinline__ float tile_sum1(const f32x16& acc, float scale, float ms) {
+  float s[2];
+#pragma unroll
+  for (int e = 0; e < 16; ++e)
+    add_to(s[e & 1], __builtin_amdgcn_exp2f(fmaf(acc[e], scale, -ms)), e < 2);
+  return s[0] + s[1];
+}
+__device__ __forceinline__ float tile_sum2(const f32x16& acc, float scale, const float (&c)[16]) {
+  float s[2];
+#pragma unroll
+  for (int e = 0; e < 16; ++e)
+    add_to(s[e & 1], __builtin_amdgcn_exp2f(fmaf(acc[e], scale, -c[e])), e < 2);
+  return s[0] + s[1];
+}
+
+// Waits for every load of the wave.  Called where only the next slab's K is
+// outstanding, a whole slab after its issue: a loop that uses registers
+// whose loads may (as far as the compiler can tell) be outstanding would
+// wait for the newer loads behind them too.
+__device__ __forceinline__ void loads_landed() {
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+}
+
+// c of the 16 rows this lane receives of a row block: 8 i + 4 half + j
+__device__ __forceinline__ void load_c(const float* cs, int half, float (&c)[16]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const f32x4 c4 = *reinterpret_cast<const f32x4*>(cs + 4 * half + 8 * i);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) c[4 * i + j] = c4[j];
+  }
+}
+
+// ---------------------------------------------------------------- pass 1
+// LDS: window rows, ms[nrb * 32] (references times scale), a flag,
+// l[wave][nrb * 64] (each wave's sums, one per lane).
+template <typename T, int D>
+__host__ __device__ constexpr size_t pass1_lds(int nrb) {
+  const size_t sums = (size_t)kSlabWaves * nrb * 64 * 4;
+  const size_t slab = (size_t)kSlab * Shape<T, D>::kQStride;   // the reference slab, before
+  return (size_t)nrb * 32 * Shape<T, D>::kQStride + (size_t)nrb * 32 * 4 + 16 +
+         (sums > slab ? sums : slab);
+}
+
+// Exact row statistics of slabs [s0, s1) against running maxima, for blocks
+// whose sums left the range of their references (or are not numbers): a
+// wave per row block, K re-read for each.
+template <typename T, int D>
+__device__ void exact_rows(const ScoreArgs& a, const T* kg, const char* qs, int s0, int s1,
+                           float2* out) {
+  using SH = Shape<T, D>;
+  const int tid = tid_here(), lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
+  for (int rb = wave; rb < a.nrb; rb += kSlabWaves) {
+    i32x4 qf[SH::kNP];
+    load_q<T, D>(qs + (rb * 32 + l32) * SH::kQStride + half * 16, qf);
+    float m = kNegBig, l = 0.f;
+    for (int slab = s0; slab < s1; ++slab) {
+      for (int cb = 0; cb < 2; cb += SH::kTB) {
+        KFrags<T, D> kf;
+        load_k<T, D>(a, kg, slab, cb, kf);
+#pragma unroll
+        for (int u = 0; u < SH::kTB; ++u) {
+          f32x16 acc = chain<T, D, true>(qf, kf[u]);
+          mask_tokens(acc, slab * kSlab + (cb + u) * 32, a.Lp);
+          float mt = acc[0];
+#pragma unroll
+          for (int e = 1; e < 16; ++e) mt = fmaxf(mt, acc[e]);
+          const float mn = fmaxf(m, mt), msn = mn * a.scale;
+          const float sum = tile_sum1(acc, a.scale, msn);
+          l = l * rescale(m, mn, msn, a.scale) + sum;
+          m = mn;
+        }
+      }
+    }
+    // the two lane halves hold the same row over other tokens
+    const float mo = other_half(m, half), lo = other_half(l, half);
+    const float mn = fmaxf(m, mo), msn = mn * a.scale;
+    l = l * rescale(m, mn, msn, a.scale) + lo * rescale(mo, mn, msn, a.scale);
+    if (half == 0) out[rb * 32 + l32] = make_float2(msn, l);
+  }
+}
+
+template <typename T, int D, bool PIPE>
+__global__ __launch_bounds__(kSlabThreads) void score_pass1(ScoreArgs a, SlabGrid sg) {
+  using SH = Shape<T, D>;
+  extern __shared__ __align__(16) unsigned char smem[];
+  char* qs = reinterpret_cast<char*>(smem);
+  float* ms_s = reinterpret_cast<float*>(smem + (size_t)a.nrb * 32 * SH::kQStride);
+  int* redo = reinterpret_cast<int*>(ms_s + a.nrb * 32);   // a sum left its range
+  float* l_s = ms_s + a.nrb * 32 + 4;
+  const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int units = kSlabWaves / sg.rs, unit = wave / sg.rs, sub = wave % sg.rs;
+  const int rb0 = a.nrb * sub / sg.rs, rb1 = a.nrb * (sub + 1) / sg.rs;
+  const char* qlane = qs + l32 * SH::kQStride + half * 16;
+  const float* mslane = ms_s + l32;
+  float* lw = l_s + wave * a.nrb * 64 + lane;
+  constexpr int kRB = 32 * SH::kQStride;      // LDS bytes of a row block
+
+  for (SlabWalk w = slab_walk(sg, slab_block());; w = slab_next(sg, w)) {
+    const T* kg = group_k<T>(a, w.lg);
+    // the segment's last slab gives the references (below); the waves then
+    // take the others, all of them whole
+    const int end = w.s1 - 1;
+    int slab = w.s0 + unit;
+    const bool any = slab < end && rb0 < rb1;
+    KFrags<T, D> kf;
+    char* ks = reinterpret_cast<char*>(l_s);
+    {
+      const T* qg = group_q<T, D>(a, w.lg);
+      i32x4 kv[slab_vecs<T, D>()], qv[kQBatch];
+      slab_issue<T, D>(a, kg, end, kv);
+      q_issue<T, D>(a, qg, tid_here(), qv);
+      if (any) load_k<T, D>(a, kg, slab, 0, kf);
+      __builtin_amdgcn_sched_barrier(0);
+      slab_commit<T, D>(ks, kv);
+      q_commit<T, D>(a, qg, qs, qv);
+    }
+    if (threadIdx.x == 0) *redo = 0;
+    __syncthreads();
+    // References: each row's max over that slab, and the slab's own sums; a
+    // wave per row block (up to two each).
+    float ref[2], rsum[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int rb = wave + i * kSlabWaves;
+      if (rb < a.nrb) {
+        i32x4 qf[SH::kNP];
+        load_q<T, D>(qlane + rb * kRB, qf);
+        f32x16 acc[2];
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+          i32x4 kf[SH::kNP];
+          load_q<T, D>(ks + (cb * 32 + l32) * SH::kQStride + half * 16, kf);
+          acc[cb] = chain<T, D, true>(qf, kf);
+        }
+        const int tb = end * kSlab;
+        if (tb + kSlab > a.Lp) {
+          mask_tokens(acc[0], tb, a.Lp);
+          mask_tokens(acc[1], tb + 32, a.Lp);
+        }
+        float mt = fmaxf(acc[0][0], acc[1][0]);
+#pragma unroll
+        for (int e = 1; e < 16; ++e) mt = fmaxf(mt, fmaxf(acc[0][e], acc[1][e]));
+        mt = fmaxf(mt, other_half(mt, half));
+        const float ms = mt * a.scale;
+        rsum[i] = tile_sum1(acc[0], a.scale, ms) + tile_sum1(acc[1], a.scale, ms);
+        ref[i] = ms;
+      }
+    }
+    __syncthreads();   // the slab's LDS becomes the sums
+    for (int rb = 0; rb < a.nrb; ++rb) lw[rb * 64] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int rb = wave + i * kSlabWaves;
+      if (rb < a.nrb) {
+        lw[rb * 64] = rsum[i];
+        if (half == 0) ms_s[rb * 32 + l32] = ref[i];
+      }
+    }
+    __syncthreads();
+
+    if (any) {
+      if constexpr (PIPE) {
+        i32x4 qf[SH::kNP];
+        load_q<T, D>(qlane + rb0 * kRB, qf);
+        f32x16 acc0 = chain<T, D, true>(qf, kf[0]), acc1;
+        int turn = wave >> 2;
+        for (;;) {
+          take_turn(turn);
+          const int next = slab + units;
+          for (int rb = rb0; rb + 1 < rb1; ++rb) {
+            const float ms = mslane[rb * 32];
+            const float l = lw[rb * 64];
+            const float s = stage1<D, true>(qf, kf[1], qlane + (rb + 1) * kRB, acc1, acc0,
+                                            a.scale, ms);
+            lw[rb * 64] = l + (s + stage1<D, false>(qf, kf[0], nullptr, acc0, acc1, a.scale, ms));
+          }
+          const int rb = rb1 - 1;
+          const float ms = mslane[rb * 32], l = lw[rb * 64];
+          const float s0 = stage1<D, true>(qf, kf[1], qlane + rb0 * kRB, acc1, acc0, a.scale, ms);
+          // the slab's K is used up: the next slab's, behind the last tile's sums
+          if (next < end) load_k<T, D>(a, kg, next, 0, kf);
+          __builtin_amdgcn_sched_barrier(0);
+          lw[rb * 64] = l + (s0 + tile_sum1(acc1, a.scale, ms));
+          if ((slab = next) >= end) break;
+          acc0 = chain<T, D, true>(qf, kf[0]);
+        }
+      } else {
+        // kTB tiles at a time
+        auto process = [&](KFrags<T, D>& k) {
+          for (int rb = rb0; rb < rb1; ++rb) {
+            const float ms = mslane[rb * 32];
+            i32x4 qf[SH::kNP];
+            load_q<T, D>(qlane + rb * kRB, qf);
+            const float l = lw[rb * 64];
+            float s = 0.f;
+#pragma unroll
+            for (int cb = 0; cb < SH::kTB; ++cb)
+              s += tile_sum1(chain<T, D, true>(qf, k[cb]), a.scale, ms);
+            lw[rb * 64] = l + s;
+          }
+        };
+        KFrags<T, D> kB;
+        for (;;) {
+          const int nx = min(slab + units, end);
+          if constexpr (SH::kTB == 2) {
+            load_k<T, D>(a, kg, nx, 0, kB);
+            process(kf);
+            loads_landed();
+            if ((slab += units) >= end) break;
+            load_k<T, D>(a, kg, min(slab + units, end), 0, kf);
+            process(kB);
+            loads_landed();
+            if ((slab += units) >= end) break;
+          } else {
+            load_k<T, D>(a, kg, slab, 1, kB);
+            process(kf);
+            loads_landed();
+            load_k<T, D>(a, kg, nx, 0, kf);
+            process(kB);
+            loads_landed();
+            if ((slab += units) >= end) break;
+          }
+        }
+      }
+    }
+    __syncthreads();
+    // the block's sums: every wave's, both lane halves, one reference per row
+    float2* out = a.part + ((size_t)w.lg * a.n_chunks_max + w.chunk) * (a.nrb * 32);
+    bool bad = false;
+    for (int r = tid_here(); r < a.nrb * 32; r += kSlabThreads) {
+      float l = 0.f;
+      const float* lr = l_s + (r >> 5) * 64 + (r & 31);
+#pragma unroll
+      for (int v = 0; v < kSlabWaves; ++v) l += lr[v * a.nrb * 64] + lr[v * a.nrb * 64 + 32];
+      out[r] = make_float2(ms_s[r], l);
+      bad |= !(l < kSumLimit);
+    }
+    if (bad) *redo = 1;
+    __syncthreads();
+    if (*redo) exact_rows<T, D>(a, kg, qs, w.s0, w.s1, out);
+    if (w.left <= 0) break;
+    __syncthreads();   // the next segment overwrites the LDS
+  }
+}
+
+// ---------------------------------------------------------------- merge
+// c_r = M_r + log2(l_r) of row r of one (layer, group) from its blocks'
+// statistics, in a fixed merge order; rows past R get +inf so that their
+// 2^(y - c) vanishes in pass 2.  The first records are loaded ahead by
+// merge_issue.
+constexpr int kMergeBatch = 8;
+__device__ __forceinline__ void merge_issue(const ScoreArgs& a, const float2* part, int n_chunks,
+                                            int c0, int r, float2 (&p)[kMergeBatch]) {
+#pragma unroll
+  for (int j = 0; j < kMergeBatch; ++j)
+    p[j] = part[(size_t)min(c0 + j, n_chunks - 1) * (a.nrb * 32) + r];
+}
+__device__ __forceinline__ float merge_row(const ScoreArgs& a, const float2* part, int n_chunks,
+                                           int r, float2 (&p)[kMergeBatch]) {
+  float Mx = kNegBig, lx = 0.f;
+  for (int c0 = 0;;) {
+    // one reference per batch; the records past the last repeat it with
+    // nothing to add
+    float mn = Mx;
+#pragma unroll
+    for (int j = 0; j < kMergeBatch; ++j) mn = fmaxf(mn, p[j].x);
+    lx *= __builtin_amdgcn_exp2f(Mx - mn);
+#pragma unroll
+    for (int j = 0; j < kMergeBatch; ++j)
+      lx += (c0 + j < n_chunks ? p[j].y : 0.f) * __builtin_amdgcn_exp2f(p[j].x - mn);
+    Mx = mn;
+    if ((c0 += kMergeBatch) >= n_chunks) break;
+    merge_issue(a, part, n_chunks, c0, r, p);
+  }
+  return (r < a.R) ? Mx + log2f(lx) : INFINITY;
+}
+
+// ---------------------------------------------------------------- pass 2
+// LDS: window rows, c[nrb * 32]; with row blocks split over waves (rs > 1)
+// the waves' token sums [wave][64].
+template <typename T, int D>
+__host__ __device__ constexpr size_t pass2_lds(int nrb) {
+  return (size_t)nrb * 32 * Shape<T, D>::kQStride + (size_t)nrb * 32 * 4 +
+         (size_t)kSlabWaves * 64 * 4;
+}
+
+template <typename T, int D, int HL, bool PIPE>
+__global__ __launch_bounds__(kSlabThreads) void score_pass2(ScoreArgs a, SlabGrid sg,
+                                                              SlabGrid sg1) {
+  using SH = Shape<T, D>;
+  extern __shared__ __align__(16) unsigned char smem[];
+  char* qs = reinterpret_cast<char*>(smem);
+  float* cs = reinterpret_cast<float*>(smem + (size_t)a.nrb * 32 * SH::kQStride);
+  float* red = cs + a.nrb * 32;
+  const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int units = kSlabWaves / sg.rs, unit = wave / sg.rs, sub = wave % sg.rs;
+  const int rb0 = a.nrb * sub / sg.rs, rb1 = a.nrb * (sub + 1) / sg.rs;
+  const char* qlane = qs + l32 * SH::kQStride + half * 16;
+  constexpr int kRB = 32 * SH::kQStride;
+
+  for (SlabWalk w = slab_walk(sg, slab_block());; w = slab_next(sg, w)) {
+    const int lg = w.lg, first = w.s0, end = w.s1;
+    const T* kg = group_k<T>(a, lg);
+    // the group's first output row: its only one, or its first head's
+    float* srow = a.sraw + (size_t)lg * (HL ? a.n_out : 1) * a.Lp;
+
+    KFrags<T, D> kf;
+    int slab = first + unit;
+    const bool any = slab < end && rb0 < rb1;
+    {
+      const T* qg = group_q<T, D>(a, lg);
+      const float2* part = a.part + (size_t)lg * a.n_chunks_max * (a.nrb * 32);
+      const int n_chunks = slab_chunks(sg1, lg), r = tid_here();
+      // one row per thread (at most 512 rows)
+      float2 pv[kMergeBatch];
+      i32x4 qv[kQBatch];
+      if (r < a.nrb * 32) merge_issue(a, part, n_chunks, 0, r, pv);
+      q_issue<T, D>(a, qg, tid_here(), qv);
+      if (any) load_k<T, D>(a, kg, slab, 0, kf);
+      __builtin_amdgcn_sched_barrier(0);
+      if (r < a.nrb * 32) cs[r] = merge_row(a, part, n_chunks, r, pv);
+      q_commit<T, D>(a, qg, qs, qv);
+    }
+    __syncthreads();
+
+    // lane's token sum(s) of a finished slab or head: tile 0's in the lower
+    // lane half, tile 1's in the upper
+    auto store = [&](float* row, float v0, float v1) {
+      const float v = add_halves(v0, v1);
+      const int tok = slab * kSlab + lane;
+      if (tok < a.Lp) row[tok] = v;
+    };
+    if (any) {
+      if constexpr (PIPE) {
+        i32x4 qf[SH::kNP];
+        load_q<T, D>(qlane + rb0 * kRB, qf);
+        f32x16 acc0 = chain<T, D, false>(qf, kf[0]), acc1;
+        int turn = wave >> 2;
+        for (;;) {
+          take_turn(turn);
+          const int next = slab + units;
+          float s0 = 0.f, s1 = 0.f;   // the lane's tokens of the two tiles
+          int left = a.upo;
+          float* hrow = srow;
+          auto flush = [&]() {
+            if (HL == kHeadBlocks && --left == 0) {
+              store(hrow, s0, s1);
+              s0 = s1 = 0.f;
+              hrow += a.Lp;
+              left = a.upo;
+            }
+          };
+          float c[16];
+          for (int rb = rb0; rb + 1 < rb1; ++rb) {
+            load_c(cs + rb * 32, half, c);
+            s0 += stage2<D, true>(qf, kf[1], qlane + (rb + 1) * kRB, acc1, acc0, a.scale, c);
+            s1 += stage2<D, false>(qf, kf[0], nullptr, acc0, acc1, a.scale, c);
+            flush();
+          }
+          load_c(cs + (rb1 - 1) * 32, half, c);
+          s0 += stage2<D, true>(qf, kf[1], qlane + rb0 * kRB, acc1, acc0, a.scale, c);
+          // the slab's K is used up: the next slab's, behind the last tile's sums
+          if (next < end) load_k<T, D>(a, kg, next, 0, kf);
+          __builtin_amdgcn_sched_barrier(0);
+          s1 += tile_sum2(acc1, a.scale, c);
+          flush();
+          if (HL == kGroup) {
+            if (sg.rs == 1) store(srow, s0, s1);
+            else red[wave * 64 + lane] = add_halves(s0, s1);
+          }
+          if ((slab = next) >= end) break;
+          acc0 = chain<T, D, false>(qf, kf[0]);
+        }
+      } else {
+        auto process = [&](KFrags<T, D>& k, int cb0) {
+          constexpr int TB = SH::kTB;
+          float s[2] = {0.f, 0.f};
+          int left = a.upo, heads = a.n_out;
+          float* hrow = srow;
+          // one 32-token tile (kTB = 1): only the lower lanes' tokens exist
+          auto put = [&](float* row) {
+            const float v = add_halves(s[0], s[1]);
+            const int tok = slab * kSlab + cb0 * 32 + lane;
+            if (tok < a.Lp && (TB == 2 || half == 0)) row[tok] = v;
+            s[0] = s[1] = 0.f;
+          };
+          for (int rb = rb0; rb < rb1; ++rb) {
+            i32x4 qf[SH::kNP];
+            load_q<T, D>(qlane + rb * kRB, qf);
+            float c[16];
+            load_c(cs + rb * 32, half, c);
+            f32x16 acc[TB];
+#pragma unroll
+            for (int cb = 0; cb < TB; ++cb) acc[cb] = chain<T, D, false>(qf, k[cb]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+#pragma unroll
+              for (int cb = 0; cb < TB; ++cb) {
+                float v[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                  v[j] = __builtin_amdgcn_exp2f(fmaf(acc[cb][4 * i + j], a.scale, -c[4 * i + j]));
+                s[cb] += (v[0] + v[1]) + (v[2] + v[3]);
+              }
+              // a head ends with this 8-row group, or with this row block;
+              // the 8-row groups past the last head's are padding
+              if ((HL == kHeadGroups || (HL == kHeadBlocks && i == 3)) && --left == 0 &&
+                  heads > 0) {
+                put(hrow);
+                hrow += a.Lp;
+                left = a.upo;
+                --heads;
+              }
+            }
+          }
+          if (HL == kGroup) {
+            if (sg.rs == 1) put(srow);
+            else {
+              const float v = add_halves(s[0], s[1]);
+              if (TB == 2 || half == 0) red[wave * 64 + cb0 * 32 + lane] = v;
+            }
+          }
+        };
+        KFrags<T, D> kB;
+        for (;;) {
+          const int nx = min(slab + units, end - 1);
+          if constexpr (SH::kTB == 2) {
+            load_k<T, D>(a, kg, nx, 0, kB);
+            process(kf, 0);
+            loads_landed();
+            if ((slab += units) >= end) break;
+            load_k<T, D>(a, kg, min(slab + units, end - 1), 0, kf);
+            process(kB, 0);
+            loads_landed();
+            if ((slab += units) >= end) break;
+          } else {
+            load_k<T, D>(a, kg, slab, 1, kB);
+            process(kf, 0);
+            loads_landed();
+            load_k<T, D>(a, kg, nx, 0, kf);
+            process(kB, 1);
+            loads_landed();
+            if ((slab += units) >= end) break;
+          }
+        }
+      }
+    }
+    if (HL == kGroup && sg.rs > 1) {
+      // one slab per unit of rs waves: add their parts in wave order
+      if (!any) red[wave * 64 + lane] = 0.f;
+      __syncthreads();
+      const int u = wave, tok = (first + u) * kSlab + lane;
+      if (u < units && first + u < end && tok < a.Lp) {
+        float v = 0.f;
+        for (int w = 0; w < sg.rs; ++w) v += red[(u * sg.rs + w) * 64 + lane];
+        srow[tok] = v;
+      }
+    }
+    if (w.left <= 0) break;
+    __syncthreads();   // the next segment overwrites the LDS
+  }
+}
+
+// ---------------------------------------------------------------- pass 2, unrolled
+// bf16 with d = 128 and up to eight row blocks, one sum per group or heads
+// of whole row blocks (PH).  The row blocks are unrolled and a row block's
+// two tiles computed together, with four accumulator tiles: each Q fragment
+// read feeds two MFMAs in a row, and the exponentials of a row block (two
+// tiles) run behind the MFMAs of the next.  7 row blocks, 28 layers of 4
+// groups, this against the rolled kernel above: 26.2 / 27.8 us at 2,915
+// tokens, 42.8 / 46.5 at 5,600, 106 / 112 at 13,679.  At 14 row blocks its
+// registers spill and the rolled one is the faster (1771 / 1792 us at
+// 140,190 tokens).
+constexpr int kUnrolledBlocks = 8;
+
+template <int NRB, bool PH>
+__global__ __launch_bounds__(kSlabThreads) void score_pass2_unrolled(ScoreArgs a, SlabGrid sg,
+                                                                     SlabGrid sg1) {
+  constexpr int NW = kSlabWaves, TB = 2;
+  constexpr int QS = Shape<__bf16, 128>::kQStride / 2;     // padded Q row
+  extern __shared__ __align__(16) unsigned char smem[];
+  __bf16* qs = reinterpret_cast<__bf16*>(smem);
+  float* cs = reinterpret_cast<float*>(smem + (size_t)NRB * 32 * QS * 2);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int half = lane >> 5, l32 = lane & 31;
-  const T* qlane = qs + l32 * QS + half * 8;
+  const __bf16* qlane = qs + l32 * QS + half * 8;
   const float* clane = cs + 4 * half;
 
-  for (long x = lo; x < hi;) {
-    const int lg = (int)(x / sg.S);
-    const int s0 = (int)(x % sg.S);
-    const int s1 = (int)min((long)sg.S, s0 + (hi - x));
-    const int layer = lg / a.G, g = lg % a.G;
-    const T* kg = group_k<T>(a, layer, g);
+  for (SlabWalk w = slab_walk(sg, slab_block());; w = slab_next(sg, w)) {
+    const int s0 = w.s0, s1 = w.s1;
+    const __bf16* kg = group_k<__bf16>(a, w.lg);
     // the group's first output row: its only one, or its first head's
-    float* srow = a.sraw + (size_t)lg * (PH ? a.n_out : 1) * a.Lp;
-
-    // the group's window rows (rows R..NRB*32 zero), in batches of at most
-    // seven 16-byte vectors per thread, each batch's loads issued before
-    // its stores
+    float* srow = a.sraw + (size_t)w.lg * (PH ? a.n_out : 1) * a.Lp;
     {
-      const T* qg = group_q<T, 128>(a, layer, g);
+      const __bf16* qg = group_q<__bf16, 128>(a, w.lg);
       constexpr int NV = NRB * 32 * 16;
-      constexpr int PER = (NV + NW * 64 - 1) / (NW * 64);
+      constexpr int PER = (NV + kSlabThreads - 1) / kSlabThreads;
       constexpr int BATCH = PER < 7 ? PER : 7;
 #pragma unroll
       for (int j0 = 0; j0 < PER; j0 += BATCH) {
         i32x4 v[BATCH];
 #pragma unroll
         for (int j = 0; j < BATCH; ++j) {
-          const int i = threadIdx.x + (j0 + j) * NW * 64, row = i >> 4, part = i & 15;
+          const int i = threadIdx.x + (j0 + j) * kSlabThreads, row = i >> 4, part = i & 15;
           v[j] = i32x4{0, 0, 0, 0};
           if (j0 + j < PER && i < NV && row < a.R)
             v[j] = *reinterpret_cast<const i32x4*>(qg + (size_t)row * 128 + part * 8);
         }
 #pragma unroll
         for (int j = 0; j < BATCH; ++j) {
-          const int i = threadIdx.x + (j0 + j) * NW * 64, row = i >> 4, part = i & 15;
+          const int i = threadIdx.x + (j0 + j) * kSlabThreads, row = i >> 4, part = i & 15;
           if (j0 + j < PER && i < NV) *reinterpret_cast<i32x4*>(qs + row * QS + part * 8) = v[j];
         }
       }
     }
-    {
-      const float2* part = a.part + (size_t)lg * a.n_chunks_max * a.Rpad;
-      for (int r = threadIdx.x; r < NRB * 32; r += NW * 64) cs[r] = merge_row(a, part, r);
+    if (threadIdx.x < NRB * 32) {
+      const float2* part = a.part + (size_t)w.lg * a.n_chunks_max * (NRB * 32);
+      const int n_chunks = slab_chunks(sg1, w.lg);
+      float2 pv[kMergeBatch];
+      merge_issue(a, part, n_chunks, 0, threadIdx.x, pv);
+      cs[threadIdx.x] = merge_row(a, part, n_chunks, threadIdx.x, pv);
     }
-    // K fragments of one slab: token block cb, row (token) l32, the 8
-    // k-slices of this lane half; tokens past L_p re-read the last token
-    // and are not stored
-    bf16x8 kf[TB][8];
-    auto load_slab = [&](int slab) {
-#pragma unroll
-      for (int cb = 0; cb < TB; ++cb) {
-        const int tok = min(slab * SLAB + cb * 32 + l32, a.Lp - 1);
-        const T* krow = kg + (int64_t)tok * a.ts + half * 8;
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk) kf[cb][kk] = *reinterpret_cast<const bf16x8*>(krow + kk * 16);
-      }
-    };
-    if (s0 + wave < s1) load_slab(s0 + wave);
+    KFrags<__bf16, 128> kf;
+    if (s0 + wave < s1) load_k<__bf16, 128>(a, kg, s0 + wave, 0, kf);
     __syncthreads();
 
     for (int slab = s0 + wave; slab < s1; slab += NW) {
@@ -124,16 +869,16 @@ __global__ __launch_bounds__(512) void score_pass2_slab(ScoreArgs a, SlabGrid sg
 #pragma unroll
       for (int cb = 0; cb < TB; ++cb) { s[cb][0] = 0.f; s[cb][1] = 0.f; }
       f32x16 accA[TB], accB[TB];
-      bf16x8 qf[8];
+      i32x4 qf[8];
       // row block 0's chain; the fragments of row block 1 are read as
       // those of row block 0 are consumed
 #pragma unroll
-      for (int kk = 0; kk < 8; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qlane + kk * 16);
+      for (int kk = 0; kk < 8; ++kk) qf[kk] = *reinterpret_cast<const i32x4*>(qlane + kk * 16);
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk) {
 #pragma unroll
-        for (int cb = 0; cb < TB; ++cb) accA[cb] = M::mma(qf[kk], kf[cb][kk], kk ? accA[cb] : f32x16{});
-        if (NRB > 1) qf[kk] = *reinterpret_cast<const bf16x8*>(qlane + 32 * QS + kk * 16);
+        for (int cb = 0; cb < TB; ++cb) accA[cb] = mma16<__bf16>(qf[kk], kf[cb][kk], kk ? accA[cb] : f32x16{});
+        if (NRB > 1) qf[kk] = *reinterpret_cast<const i32x4*>(qlane + 32 * QS + kk * 16);
       }
       __builtin_amdgcn_sched_barrier(0);
       // stage rb: MFMAs of row block rb+1 (reading the Q fragments of rb+2
@@ -154,8 +899,8 @@ __global__ __launch_bounds__(512) void score_pass2_slab(ScoreArgs a, SlabGrid sg
         for (int kk = 0; kk < 8; ++kk) {
           if (rb + 1 < NRB) {
 #pragma unroll
-            for (int cb = 0; cb < TB; ++cb) nxt[cb] = M::mma(qf[kk], kf[cb][kk], kk ? nxt[cb] : f32x16{});
-            if (rb + 2 < NRB) qf[kk] = *reinterpret_cast<const bf16x8*>(qlane + (rb + 2) * 32 * QS + kk * 16);
+            for (int cb = 0; cb < TB; ++cb) nxt[cb] = mma16<__bf16>(qf[kk], kf[cb][kk], kk ? nxt[cb] : f32x16{});
+            if (rb + 2 < NRB) qf[kk] = *reinterpret_cast<const i32x4*>(qlane + (rb + 2) * 32 * QS + kk * 16);
           }
 #pragma unroll
           for (int cb = 0; cb < TB; ++cb)
@@ -187,7 +932,7 @@ __global__ __launch_bounds__(512) void score_pass2_slab(ScoreArgs a, SlabGrid sg
           for (int cb = 0; cb < TB; ++cb) {
             const float sc = s[cb][0] + s[cb][1];
             const float v = sc + other_half(sc, half);
-            const int tok = slab * SLAB + cb * 32 + l32;
+            const int tok = slab * kSlab + cb * 32 + l32;
             if ((cb & 1) == half && tok < a.Lp) hrow[tok] = v;
             s[cb][0] = 0.f;
             s[cb][1] = 0.f;
@@ -195,8 +940,8 @@ __global__ __launch_bounds__(512) void score_pass2_slab(ScoreArgs a, SlabGrid sg
         }
         __builtin_amdgcn_sched_barrier(0);
       }
-      const int t0 = slab * SLAB;
-      if (slab + NW < s1) load_slab(slab + NW);
+      const int t0 = slab * kSlab;
+      if (slab + NW < s1) load_k<__bf16, 128>(a, kg, slab + NW, 0, kf);
       // lanes l and l ^ 32 hold the same token's two row halves; half h
       // stores token block h
       if (!PH) {
@@ -209,18 +954,222 @@ __global__ __launch_bounds__(512) void score_pass2_slab(ScoreArgs a, SlabGrid sg
         }
       }
     }
-    x += s1 - s0;
-    // the next segment overwrites the rows and c in LDS
-    __syncthreads();
+    if (w.left <= 0) break;
+    __syncthreads();   // the next segment overwrites the LDS
   }
+}
+
+template <int NRB>
+void launch_unrolled(const ScoreArgs& a, const SlabLaunch& p2, const SlabGrid& g1,
+                     hipStream_t st) {
+  const size_t lds = (size_t)NRB * 32 * (Shape<__bf16, 128>::kQStride + 4);
+  if (a.n_out > 1)
+    score_pass2_unrolled<NRB, true><<<p2.blocks, kSlabThreads, lds, st>>>(a, p2.g, g1);
+  else
+    score_pass2_unrolled<NRB, false><<<p2.blocks, kSlabThreads, lds, st>>>(a, p2.g, g1);
+}
+
+// ---------------------------------------------------------------- small calls
+// Few slabs for the GPU: a launch is then its start and one short chain of
+// dependent steps, and the persistent kernels' steps (window rows to LDS,
+// references, the slab loop) come one after another.  Here the waves of a
+// block have a row block each (with few row blocks, several waves share one
+// and split its tokens), whose window rows go straight into registers, and
+// K is read once through LDS.
+
+// Rows [0, n) of K from token t0 on to LDS, coalesced; n_rows rows are
+// written, those past n repeating the last.
+template <typename T, int D>
+__device__ __forceinline__ void stage_rows(const ScoreArgs& a, const T* kg, int t0, int n,
+                                           int n_rows, char* ks) {
+  using SH = Shape<T, D>;
+  constexpr int VPR = SH::kRowBytes / 16, BATCH = 8;
+  constexpr int NT = kSmallWaves * 64;
+  const int nv = n_rows * VPR;
+  const char* base = reinterpret_cast<const char*>(kg + (int64_t)t0 * a.ts);
+  for (int i0 = threadIdx.x; i0 < nv; i0 += BATCH * NT) {
+    i32x4 v[BATCH];
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) {
+      const int i = i0 + j * NT, row = min(i / VPR, n - 1), part = i % VPR;
+      if (i < nv)
+        v[j] = *reinterpret_cast<const i32x4*>(base + (int64_t)row * (a.ts * (int64_t)sizeof(T)) +
+                                               part * 16);
+    }
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) {
+      const int i = i0 + j * NT, row = i / VPR, part = i % VPR;
+      if (i < nv) *reinterpret_cast<i32x4*>(ks + row * SH::kQStride + part * 16) = v[j];
+    }
+  }
+}
+
+// The wave's row block of window rows, zero past R.
+template <typename T, int D>
+__device__ __forceinline__ void load_rows(const ScoreArgs& a, const T* qg, int rb,
+                                          i32x4 (&qf)[Shape<T, D>::kNP]) {
+  const int lane = threadIdx.x & 63, half = lane >> 5, row = rb * 32 + (lane & 31);
+  const char* q = reinterpret_cast<const char*>(qg + (size_t)min(row, a.R - 1) * D) + half * 16;
+#pragma unroll
+  for (int j = 0; j < Shape<T, D>::kNP; ++j) {
+    qf[j] = *reinterpret_cast<const i32x4*>(q + j * 32);
+    if (row >= a.R) qf[j] = i32x4{0, 0, 0, 0};
+  }
+}
+
+// Pass 1: block (lg, chunk) of per_lg = ceil(L_p / 256) chunks; exact
+// running maxima, slab by slab.  parts waves share a row block, slab by slab.
+template <typename T, int D>
+__global__ __launch_bounds__(kSmallWaves * 64) void score_pass1_small(ScoreArgs a, int per_lg,
+                                                                      int parts) {
+  using SH = Shape<T, D>;
+  __shared__ float2 ml[kSmallWaves * 32];
+  extern __shared__ __align__(16) unsigned char smem[];
+  char* ks = reinterpret_cast<char*>(smem);
+  const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int part = wave / a.nrb, rb = wave - part * a.nrb;
+  const int b = slab_block(), lg = b / per_lg, chunk = b - lg * per_lg;
+  const int t0 = chunk * kSmallRows, n = min(kSmallRows, a.Lp - t0);
+  const int slabs = (n + kSlab - 1) / kSlab;
+  i32x4 qf[SH::kNP];
+  load_rows<T, D>(a, group_q<T, D>(a, lg), rb, qf);
+  stage_rows<T, D>(a, group_k<T>(a, lg), t0, n, slabs * kSlab, ks);
+  __syncthreads();
+  float m = kNegBig, l = 0.f;
+  const char* krow = ks + l32 * SH::kQStride + half * 16;
+  for (int s = part < parts ? part : slabs; s < slabs; s += parts) {
+    f32x16 acc[2];
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) {
+      i32x4 kf[SH::kNP];
+      load_q<T, D>(krow + (s * kSlab + cb * 32) * SH::kQStride, kf);
+      acc[cb] = chain<T, D, true>(qf, kf);
+    }
+    if ((s + 1) * kSlab > n) {
+      mask_tokens(acc[0], t0 + s * kSlab, a.Lp);
+      mask_tokens(acc[1], t0 + s * kSlab + 32, a.Lp);
+    }
+    float mt = fmaxf(acc[0][0], acc[1][0]);
+#pragma unroll
+    for (int e = 1; e < 16; ++e) mt = fmaxf(mt, fmaxf(acc[0][e], acc[1][e]));
+    const float mn = fmaxf(m, mt), msn = mn * a.scale;
+    const float sum = tile_sum1(acc[0], a.scale, msn) + tile_sum1(acc[1], a.scale, msn);
+    l = l * rescale(m, mn, msn, a.scale) + sum;
+    m = mn;
+  }
+  const float mo = other_half(m, half), lo = other_half(l, half);
+  float mn = fmaxf(m, mo), msn = mn * a.scale;
+  l = l * rescale(m, mn, msn, a.scale) + lo * rescale(mo, mn, msn, a.scale);
+  if (parts > 1) {   // the row block's waves, in order (an idle one adds 0)
+    if (half == 0) ml[wave * 32 + l32] = make_float2(mn, l);
+    __syncthreads();
+    if (part > 0) return;
+    for (int p = 1; p < parts; ++p) {
+      const float2 o = ml[(p * a.nrb + rb) * 32 + l32];
+      const float mm = fmaxf(mn, o.x);
+      msn = mm * a.scale;
+      l = l * rescale(mn, mm, msn, a.scale) + o.y * rescale(o.x, mm, msn, a.scale);
+      mn = mm;
+    }
+  } else if (part > 0) {
+    return;
+  }
+  if (half == 0)
+    a.part[((size_t)lg * a.n_chunks_max + chunk) * (a.nrb * 32) + rb * 32 + l32] =
+        make_float2(msn, l);
+}
+
+// Pass 2: block (lg, slab); the records of pass 1's division sg1.  n_out
+// outputs, of upo row blocks each.  With at most four row blocks two waves
+// share one, a tile each.
+template <typename T, int D>
+__global__ __launch_bounds__(kSmallWaves * 64) void score_pass2_small(ScoreArgs a, int S,
+                                                                      SlabGrid sg1) {
+  using SH = Shape<T, D>;
+  __shared__ __align__(16) float cs[kSmallWaves * 32];
+  __shared__ float red[kSmallWaves * 64];
+  extern __shared__ __align__(16) unsigned char smem[];
+  char* ks = reinterpret_cast<char*>(smem);
+  const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool split = 2 * a.nrb <= kSmallWaves;
+  const int part = wave / a.nrb, rb = wave - part * a.nrb;
+  const int b = slab_block(), lg = b / S, slab = b - lg * S;
+  const int t0 = slab * kSlab;
+  const float2* rec = a.part + (size_t)lg * a.n_chunks_max * (a.nrb * 32);
+  const int n_chunks = slab_chunks(sg1, lg), row = threadIdx.x;
+  float2 pv[kMergeBatch];
+  i32x4 qf[SH::kNP];
+  if (row < a.nrb * 32) merge_issue(a, rec, n_chunks, 0, row, pv);
+  load_rows<T, D>(a, group_q<T, D>(a, lg), rb, qf);
+  stage_rows<T, D>(a, group_k<T>(a, lg), t0, min(kSlab, a.Lp - t0), kSlab, ks);
+  if (row < a.nrb * 32) cs[row] = merge_row(a, rec, n_chunks, row, pv);
+  __syncthreads();
+  if (part < (split ? 2 : 1)) {
+    float c[16];
+    load_c(cs + rb * 32, half, c);
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) {
+      if (split && part != cb) continue;
+      i32x4 kf[SH::kNP];
+      load_q<T, D>(ks + (cb * 32 + l32) * SH::kQStride + half * 16, kf);
+      const float s = tile_sum2(chain<T, D, false>(qf, kf), a.scale, c);
+      const float v = s + other_half(s, half);
+      if (half == 0) red[rb * 64 + cb * 32 + l32] = v;
+    }
+  }
+  __syncthreads();
+  if (wave >= a.n_out || t0 + lane >= a.Lp) return;
+  const int upo = a.n_out == 1 ? a.nrb : a.upo;
+  float v = 0.f;
+  for (int u = wave * upo; u < (wave + 1) * upo; ++u) v += red[u * 64 + lane];
+  a.sraw[((size_t)lg * a.n_out + wave) * a.Lp + t0 + lane] = v;
+}
+
+inline void run_unrolled(const ScoreArgs& a, const SlabLaunch& p2, const SlabGrid& g1,
+                         hipStream_t st) {
+  switch (a.nrb) {
+#define STARKV_NRB(n) \
+  case n: launch_unrolled<n>(a, p2, g1, st); break;
+    STARKV_NRB(1) STARKV_NRB(2) STARKV_NRB(3) STARKV_NRB(4) STARKV_NRB(5) STARKV_NRB(6)
+    STARKV_NRB(7) STARKV_NRB(8)
+#undef STARKV_NRB
+  }
+}
+
+template <typename T, int D>
+int run_passes(const ScoreArgs& a, const SlabLaunch& p1, const SlabLaunch& p2, hipStream_t st) {
+  constexpr bool kPipe = sizeof(T) == 2;   // tiles interleaved
+  const size_t lds2 = pass2_lds<T, D>(a.nrb);
+  if (p1.small) {
+    const size_t lds = (size_t)kSmallRows * Shape<T, D>::kQStride;
+    const int slabs = kSmallRows / kSlab, parts = kSmallWaves / a.nrb;
+    score_pass1_small<T, D><<<p1.blocks, kSmallWaves * 64, lds, st>>>(a, p1.g.per_lg,
+                                                                      parts < slabs ? parts : slabs);
+  } else {
+    score_pass1<T, D, kPipe><<<p1.blocks, kSlabThreads, pass1_lds<T, D>(a.nrb), st>>>(a, p1.g);
+  }
+  if (p2.small)
+    score_pass2_small<T, D><<<p2.blocks, kSmallWaves * 64,
+                              (size_t)kSlab * Shape<T, D>::kQStride, st>>>(a, p2.g.S, p1.g);
+  else if (kPipe && D == 128 && a.nrb <= kUnrolledBlocks && (a.n_out == 1 || a.W % 32 == 0))
+    run_unrolled(a, p2, p1.g, st);
+  else if (a.n_out == 1)
+    score_pass2<T, D, kGroup, kPipe><<<p2.blocks, kSlabThreads, lds2, st>>>(a, p2.g, p1.g);
+  else if (a.W % 32 == 0)
+    score_pass2<T, D, kHeadBlocks, kPipe><<<p2.blocks, kSlabThreads, lds2, st>>>(a, p2.g, p1.g);
+  else
+    score_pass2<T, D, kHeadGroups, false><<<p2.blocks, kSlabThreads, lds2, st>>>(a, p2.g, p1.g);
+  return (int)hipGetLastError();
 }
 
 }  // namespace
 
-// Pass 2 on the slab kernel: R = NRB*32-padded rows, NRB <= kSlabMaxNrb;
-// per-head subspaces need each head's rows to be whole row blocks (n_part
-// 1, upo row blocks per head).
-constexpr int kSlabMaxNrb = 14;
-int run_pass2_slab(const ScoreArgs& a, int n_layers, int n_cu, hipStream_t st);
+// The two passes, one translation unit per element type.
+int run_score_bf16(const ScoreArgs& a, int d, const SlabLaunch& p1, const SlabLaunch& p2,
+                   hipStream_t st);
+int run_score_f32(const ScoreArgs& a, int d, const SlabLaunch& p1, const SlabLaunch& p2,
+                  hipStream_t st);
 
 }  // namespace starkv

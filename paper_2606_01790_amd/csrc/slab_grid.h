@@ -1,0 +1,166 @@
+// How a scoring pass's 64-token slabs are divided into blocks, and how a
+// block walks its share.  Host code, kernels and tests share this file.
+#pragma once
+#include <algorithm>
+#include <cstdint>
+
+#ifdef __HIPCC__
+#define STARKV_HD __host__ __device__
+#else
+#define STARKV_HD
+#endif
+
+namespace starkv {
+
+constexpr int kSlab = 64;           // tokens per slab
+constexpr int kSlabWaves = 8;       // waves of a persistent block
+constexpr int kSmallRows = 256;     // tokens of a small-call block in pass 1
+constexpr int kSmallWaves = 8;      // row blocks (a wave each) of a small-call block at most
+
+STARKV_HD inline int slab_min(int a, int b) { return a < b ? a : b; }
+
+// A pass's division of the slabs into blocks (slab_grid below):
+// per_lg > 0: per_lg blocks per (layer, group), of q slabs and one more in
+// the first r of them; per_lg = 0: the same over all slabs, so that a block
+// may cross into the next (layer, group).
+struct SlabGrid {
+  int S;        // 64-token slabs per (layer, group)
+  int per_lg, q, r;
+  int rs;       // waves that share a slab, each with its part of the row blocks
+};
+
+// A pass's launch: its division and block count.
+struct SlabLaunch {
+  SlabGrid g;
+  int blocks;
+  bool small = false;   // the small-call kernels
+};
+
+// The block of slab x under per_lg = 0.  32 bits: the scores of 2^31 slabs
+// would not fit the GPU's memory.
+STARKV_HD inline int slab_owner(const SlabGrid& g, int x) {
+  const int y = x - g.r * (g.q + 1);
+  return y < 0 ? x / (g.q + 1) : g.r + y / g.q;
+}
+
+// A block's walk over its slabs: segments of one (layer, group) each.
+struct SlabWalk {
+  int lg, s0, s1;   // this segment
+  int chunk;        // the block's index among the blocks of lg
+  int left;         // slabs after this segment
+};
+
+STARKV_HD inline SlabWalk slab_walk(const SlabGrid& g, int b) {
+  const bool aligned = g.per_lg > 0;
+  const int x = b * g.q + slab_min(b, g.r);              // crossing: the first slab
+  const int lg = aligned ? b / g.per_lg : x / g.S;
+  const int i = b - lg * g.per_lg;                       // aligned: the block of lg
+  const int s0 = aligned ? i * g.q + slab_min(i, g.r) : x - lg * g.S;
+  const int n = g.q + ((aligned ? i : b) < g.r);
+  const int s1 = slab_min(g.S, s0 + n);
+  const int chunk = aligned ? i : b - slab_owner(g, lg * g.S);
+  return SlabWalk{lg, s0, s1, chunk, n - (s1 - s0)};
+}
+
+// The walk's next segment, where left > 0.
+STARKV_HD inline SlabWalk slab_next(const SlabGrid& g, const SlabWalk& w) {
+  const int n = slab_min(g.S, w.left);
+  return SlabWalk{w.lg + 1, 0, n, 0, w.left - n};
+}
+
+// Blocks whose slabs include some of (layer, group) lg's.
+STARKV_HD inline int slab_chunks(const SlabGrid& g, int lg) {
+  if (g.per_lg > 0) return g.per_lg;
+  return slab_owner(g, lg * g.S + g.S - 1) - slab_owner(g, lg * g.S) + 1;
+}
+
+// A pass's blocks (one per CU at a time: the window rows fill the LDS).
+// Either `per_lg` blocks per (layer, group), or one block per CU on equal
+// ranges that cross groups.  The unit of the estimate is an eighth of a
+// slab round, the time the block's eight waves take for a slab each; every
+// group a block touches costs its window rows and the rounding of its
+// slabs to whole rounds, every block its start.  Equal ranges win when the
+// slabs are many rounds per CU, aligned blocks when they are few (28 layers
+// of 4 groups: aligned at one 1920x1080 frame, 30.0 us against 35.6 in pass
+// 1 and 26.2 against 28.1 in pass 2; equal ranges at 30 frames).  In
+// between they tie to within 5% either way and aligned blocks are taken.
+// With at most four slabs in a block, several waves share a slab, each with
+// its part of the row blocks.
+inline SlabLaunch slab_grid(int Lp, int nlg, int nrb, int n_cu, int max_per_lg, bool share) {
+  SlabLaunch l;
+  SlabGrid& g = l.g;
+  g.S = (Lp + kSlab - 1) / kSlab;
+  constexpr int kStart = 8;   // a block's start: about one round
+  auto waves_per_slab = [&](int64_t slabs) {
+    int rs = 1;
+    while (share && rs * 2 * slabs <= kSlabWaves && rs * 2 <= nrb) rs *= 2;
+    return rs;
+  };
+  auto rounds8 = [&](int64_t slabs) {
+    const int rs = waves_per_slab(slabs);
+    return rs > 1 ? 8 / rs : (slabs + kSlabWaves - 1) / kSlabWaves * 8;
+  };
+  const int64_t total = (int64_t)g.S * nlg;
+  int64_t best = -1;
+  const int64_t p_max = std::min<int64_t>({(int64_t)max_per_lg, (int64_t)g.S,
+                                           std::max<int64_t>(1, 4L * n_cu / nlg)});
+  for (int64_t p = 1; p <= p_max; ++p) {
+    const int64_t q = (g.S + p - 1) / p;
+    const int64_t cost = (p * nlg + n_cu - 1) / n_cu * (rounds8(q) + kStart);
+    if (best < 0 || cost <= best) {
+      best = cost;
+      g.per_lg = (int)p;
+      g.q = (int)(g.S / p);
+      g.r = (int)(g.S % p);
+      g.rs = waves_per_slab(q);
+      l.blocks = (int)(p * nlg);
+    }
+  }
+  if (total > n_cu) {
+    const int64_t q = (total + n_cu - 1) / n_cu, q_min = total / n_cu;
+    const int64_t segs = (q + g.S - 2) / g.S + 1;
+    const int64_t chunks = (g.S + q_min - 2) / q_min + 1;   // blocks per group at most
+    const int64_t cost = (q + kSlabWaves - 1) / kSlabWaves * 8 + kStart + (segs - 1) * (8 + kStart);
+    if (chunks <= max_per_lg && cost < best) {
+      g.per_lg = 0;
+      g.q = (int)q_min;
+      g.r = (int)(total - q_min * n_cu);
+      g.rs = 1;
+      l.blocks = n_cu;
+    }
+  }
+  return l;
+}
+
+// The two passes' launches for n_layers * G groups of nrb row blocks, at most
+// max_chunks records per group in the workspace.  one_sum: one output per
+// group (waves may then share a slab in pass 2); whole_blocks: an output's
+// rows are whole row blocks.
+//
+// The small-call kernels run one short step per block and win while the
+// blocks run side by side: pass 1 (a block per CU fits beside another, but
+// slower) up to one block per CU, pass 2 up to one and a half, or one with
+// fewer than four row blocks (368 blocks: 7.9 / 8.4 at four row blocks, 7.6
+// / 6.7 at two, 7.3 / 5.5 at one).  28 heads on
+// 4 groups, d = 128, us per launch, small against persistent: pass 1 at 192
+// blocks 8.0 / 11.0, 240 and 264 blocks 13.5 / 11.5, 288 blocks 13.0 / 11.2;
+// pass 2 at 184 blocks 6.1 / 7.9, 368 blocks 8.8 / 9.3, 528 blocks 11.1 / 9.8.
+inline void slab_launches(int Lp, int nlg, int nrb, int n_cu, int max_chunks, bool one_sum,
+                          bool whole_blocks, SlabLaunch* p1, SlabLaunch* p2) {
+  *p1 = slab_grid(Lp, nlg, nrb, n_cu, max_chunks, true);
+  *p2 = slab_grid(Lp, nlg, nrb, n_cu, 1 << 30, one_sum);
+  if (nrb > kSmallWaves) return;
+  const int64_t chunks = (Lp + kSmallRows - 1) / kSmallRows;
+  if (chunks <= max_chunks && chunks * nlg <= n_cu) {
+    p1->small = true;
+    p1->g.per_lg = (int)chunks;
+    p1->blocks = (int)(chunks * nlg);
+  }
+  const int64_t p2_small = nrb >= 4 ? n_cu + n_cu / 2 : n_cu;
+  if (whole_blocks && (int64_t)p2->g.S * nlg <= p2_small) {
+    p2->small = true;
+    p2->blocks = p2->g.S * nlg;
+  }
+}
+
+}  // namespace starkv

@@ -134,3 +134,29 @@ def test_statistics_block_shape(tmp_path):
     got = [tuple(map(int, line.split())) for line in r.stdout.splitlines()]
     assert got == [(-(-n // 8), n + 1 - (-n // 8)) for n in subs], list(zip(subs, got))
     assert got[1][1] == 6 and got[7][1] == 33
+
+
+def test_scoring_slab_division(tmp_path):
+    """Every slab of every (layer, group) belongs to exactly one block of each
+    pass, a group's records of pass 1 are numbered from 0 in block order and
+    fit the workspace, and waves share a slab only where the block's slabs
+    fit; over token counts around the slab and record sizes, group counts
+    around the CU count, and all three divisions of each pass."""
+    exe = _build(tmp_path, "slab_grid", [os.path.join(HOST, "slab_grid_driver.cpp")],
+                 sanitize=True)
+    lines = []
+    for Lp in [1, 63, 64, 65, 255, 256, 257, 511, 2915, 13679, 40845, 140190]:
+        for nlg in [1, 2, 3, 4, 7, 12, 64, 112, 255, 256, 257, 448, 1000]:
+            for nrb in (1, 7, 8, 9, 14, 16):
+                for n_cu in (256, 304, 1):
+                    one = (Lp + nlg + nrb) % 2
+                    lines.append((Lp, nlg, nrb, n_cu, -(-Lp // 256), one, 1 if one else nrb % 2))
+    r = subprocess.run([exe], input="".join(" ".join(map(str, x)) + "\n" for x in lines),
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
+    out = r.stdout.splitlines()
+    assert len(out) == len(lines)
+    bad = [(x, o) for x, o in zip(lines, out) if not o.startswith("ok ")]
+    assert not bad, bad[:10]
+    for p in (1, 2):
+        assert {o.split()[p] for o in out} == {"small", "aligned", "crossing"}

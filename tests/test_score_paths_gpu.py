@@ -1,0 +1,85 @@
+"""The scoring passes' launch forms against a 64-bit softmax: small-call
+kernels, aligned and crossing persistent blocks, slabs shared by waves, every
+output layout, and row sums that leave the range of a block's reference."""
+
+from __future__ import annotations
+
+import math
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(nl, H, G, d, W, Lp, dtype, per_head, spike):
+    import torch
+    from paper_2606_01790_amd import starkv as sk
+    g = torch.Generator(device="cuda").manual_seed(nl * 1000 + Lp)
+    tt = torch.float32 if dtype == "f32" else torch.bfloat16
+    L = Lp + W
+    k = torch.randn(nl, G, L + 3, d, generator=g, device="cuda").to(tt)
+    q = torch.randn(nl, H, W, d, generator=g, device="cuda").to(tt)
+    if spike:
+        # keys that grow along the cache and one far above the rest, neither
+        # in a block's last slab
+        k[:, :, Lp // 3] *= spike
+        k[:, :, :Lp // 2] *= torch.linspace(0.1, 4.0, Lp // 2, device="cuda").to(tt)[:, None]
+    dims = sk.make_dims(nl, H, G, d, L, W, sk.F32 if dtype == "f32" else sk.BF16, per_head)
+    p = sk.params_default()
+    lay = sk.contiguous_layout(k, dims)
+    S = torch.empty(nl, dims.Ns, Lp, device="cuda")
+    sbar = torch.empty(nl, Lp, device="cuda")
+    gstar = torch.empty(nl, Lp, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(sk.workspace_bytes(dims), dtype=torch.uint8, device="cuda")
+    sk.score(dims, p, q, k, lay, S, sbar, gstar, ws)
+    torch.cuda.synchronize()
+    ref = torch.zeros(nl, dims.Ns, Lp, dtype=torch.float64, device="cuda")
+    hps = H // dims.Ns
+    ymax = 0.0
+    for l in range(nl):
+        for h in range(H):
+            kk = k[l, h // (H // G), :Lp].double()
+            y = (q[l, h].double() @ kk.t().contiguous()) / math.sqrt(d)
+            ymax = max(ymax, float(y.abs().max()) * math.log2(math.e))
+            ref[l, h // hps] += torch.softmax(y, 1).sum(0)
+    ref = torch.nn.functional.avg_pool1d(ref, 5, stride=1, padding=2) / hps
+    # per value: the rounding of y, of c and of their difference, each up to
+    # 2^-24 of a magnitude of at most ymax + 32 (c adds log2 of the row sum),
+    # the fp32 dot product's d steps, and the sums over rows; doubled
+    tol = 2 * (3 * (ymax + 32) + d * ymax / 8 + 64) * 2.0 ** -24
+    # values far below the row's mass may underflow to zero on the way
+    err = ((S.double() - ref).abs() / (ref + 1e-25)).max()
+    assert float(err) <= tol, (float(err), tol)
+
+
+# (layers, H, G, d, W, Lp, dtype, per_head)
+FORMS = [
+    (1, 28, 4, 128, 32, 700, "bf16", False),      # small kernels, nrb 7
+    (2, 28, 4, 128, 32, 2915, "bf16", False),     # small pass 1, pass 2 above a block per CU
+    (2, 8, 8, 64, 8, 130, "bf16", False),         # small, one row block, ragged
+    (1, 8, 2, 128, 32, 321, "f32", False),        # small, fp32
+    (1, 8, 2, 128, 32, 321, "bf16", True),        # small, per head
+    (1, 8, 2, 128, 16, 321, "bf16", True),        # small pass 1, 8-row heads in pass 2
+    (40, 14, 2, 64, 32, 700, "bf16", False),      # aligned, slabs shared by waves
+    (28, 28, 4, 128, 32, 1025, "bf16", False),    # aligned
+    (28, 28, 4, 128, 32, 1025, "bf16", True),
+    (28, 12, 2, 128, 24, 1025, "bf16", True),     # 8-row heads that cross row blocks
+    (3, 2, 2, 64, 512, 14001, "bf16", False),     # sixteen row blocks, few groups
+    (1, 15, 1, 128, 32, 30001, "bf16", False),    # fifteen row blocks, persistent
+    (11, 32, 8, 64, 16, 9001, "bf16", False),     # ranges crossing groups
+    (9, 16, 4, 128, 8, 9001, "f32", False),       # fp32, one 32-token tile at a time
+    (9, 16, 4, 64, 8, 9001, "f32", True),
+]
+
+
+@pytest.mark.parametrize("form", FORMS, ids=["-".join(map(str, f)) for f in FORMS])
+def test_score_form(form):
+    _run(*form, spike=0.0)
+
+
+@pytest.mark.parametrize("form", [FORMS[0], FORMS[7], FORMS[8], FORMS[11], FORMS[12], FORMS[13]],
+                         ids=["small", "aligned", "per-head", "persistent", "crossing", "f32"])
+def test_sums_beyond_the_reference(form):
+    """Logits that rise by more than 64 log2 units inside a block: its row
+    sums are redone against running maxima."""
+    _run(*form, spike=24.0)
