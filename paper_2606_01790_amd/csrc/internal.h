@@ -55,8 +55,10 @@ struct StateHeader {
   int32_t n;          // compression calls so far in this trajectory
   int32_t nf;         // token count of the frame m_g was built from
   int32_t arrive;     // blocks of the running update that have finished
-  int32_t pad[10];
+  double ent[4];      // the running update's entropy sums (zero between updates)
+  int32_t pad[2];
 };
+static_assert(sizeof(StateHeader) == 64, "the state block's header");
 constexpr int32_t kStateMagic = 0x53544B56;  // "STKV"
 size_t state_stride(int G, int frame_cap);
 size_t state_mibar_off();

@@ -1,6 +1,7 @@
 // Online statistics of one step (sec. 3.4-3.6).
 //
-// stats kernel, G + 1 + ceil(G / 8) blocks per layer, 1024 threads (512 or
+// stats kernel, G + 1 + ceil(G / 8) blocks per layer (and three more at long
+// contexts, which share the entropy sum), 1024 threads (512 or
 // 256 when the blocks outnumber the CUs, see StatsShape), where G is the
 // call's number of scoring subspaces (the KV groups, or the query heads).
 // Block g of a layer computes:
@@ -54,6 +55,8 @@ namespace {
 
 struct SpanSet {
   int32_t n;
+  int32_t dense;   // adjacent spans: visual index i is token start[0] + i
+  int32_t same;    // spans of one shape: the position in the frame is i modulo its size
   int32_t start[STARKV_MAX_SPANS];
   int32_t rows[STARKV_MAX_SPANS];
   int32_t cols[STARKV_MAX_SPANS];
@@ -66,6 +69,7 @@ struct FinalArgs {
   char* state;
   size_t state_stride;
   int G, sc, nf;      // nf = current frame tokens, or -1
+  int n_ent, Lp;
   float rho_mi, tau, eps, lam, t_min, t_max;
   int n_warmup, n_ramp;
 };
@@ -79,6 +83,7 @@ struct StatsArgs {
   size_t m_off;
   int G, Lp, nbins, grid, cur, frame_cap, sc;
   int n_stab;             // stability blocks, kStabSubspaces subspaces each
+  int n_ent;              // entropy blocks
   int n_layers;
   int aeb;                // starkv_aeb_mode
   float rho_t, eps;
@@ -88,6 +93,7 @@ struct StatsArgs {
 
 constexpr int kBatch = 8;                 // loads in flight per thread
 constexpr int kKeyBatch = 8;              // keys per thread per rank-binning step
+constexpr int kFuse = 4;                  // keys per thread per step of the fused pass
 constexpr int kLoadBatch = 16;            // loads in flight in the first pass over S
 constexpr int kDirect = 256;              // candidates ranked directly, no more digits
 constexpr int kTieChunks = 256;           // visual-index chunks for locating tie splits
@@ -95,14 +101,15 @@ constexpr int kFirstDigitBins = 4096;     // the 12-bit first digit
 
 // Three block shapes.  The wide one (1024 threads, 152 KiB of LDS) fills a
 // CU and serves calls whose blocks fit on the GPU at once; the narrow one
-// (512 threads, 61 KiB) runs two blocks per CU for calls with more blocks
+// (512 threads, 65 KiB) runs two blocks per CU for calls with more blocks
 // than CUs (a subspace per head), and needs n_bins <= kNarrowMaxBins; the
-// small one (256 threads, 29 KiB, at most 128 VGPRs) runs four per CU for
+// small one (256 threads, 31 KiB, at most 128 VGPRs) runs four per CU for
 // calls with more blocks than two per CU, and needs n_bins <= kSmallMaxBins
 // and grid^2 <= kSmallMaxCells.
 //   kHistInts  digit or joint histograms
 //   kKeyCache  visual keys kept in LDS
-//   kCand      keys in the edges' first-digit buckets
+//   kCand      keys in the edges' first-digit buckets, or (uncached keys, whose
+//              candidates take the key cache) the cells of a frame's tokens
 //   kJointOff  joint histogram slot when digits follow
 //   kMaxTies   tied edges whose split counts live in the key cache
 template <int NT>
@@ -115,12 +122,12 @@ struct StatsShape<1024> {
 template <>
 struct StatsShape<512> {
   static constexpr int kHistInts = 4096 + kNarrowMaxBins * 256, kKeyCache = 6 * 1024,
-                       kCand = 1024, kJointOff = 4096, kMaxTies = kNarrowMaxBins - 1;
+                       kCand = 2048, kJointOff = 4096, kMaxTies = kNarrowMaxBins - 1;
 };
 template <>
 struct StatsShape<256> {
   static constexpr int kHistInts = 4096 + kSmallMaxBins * kSmallMaxCells, kKeyCache = 2048,
-                       kCand = 512, kJointOff = 4096, kMaxTies = kSmallMaxBins - 1;
+                       kCand = 1024, kJointOff = 4096, kMaxTies = kSmallMaxBins - 1;
 };
 // The fused selection's key cache follows its fixed LDS in the wide shape's
 // dynamic LDS.
@@ -155,7 +162,13 @@ __device__ inline int wave_sum_i(int v) {
   return v;
 }
 
-// Layer and block-of-layer of this workgroup (the grid order above).
+// Normalised entropy from e = sum p log(p + eps) over L_p tokens.
+__device__ inline float entropy_stat(double e, int Lp) {
+  return Lp > 1 ? (float)fmin(1.0, fmax(0.0, -e / log((double)Lp))) : 0.f;
+}
+
+// Layer and block-of-layer of this workgroup (the grid order above); further
+// entropy blocks of a layer come as blocks G + 1 + n_stab and on.
 __device__ __forceinline__ void stats_block(const StatsArgs& a, int* layer, int* g) {
   const int id = blockIdx.x;
   const int n_mi = a.G * a.n_layers;
@@ -163,7 +176,7 @@ __device__ __forceinline__ void stats_block(const StatsArgs& a, int* layer, int*
     *layer = id / a.G;
     *g = id - *layer * a.G;
   } else {
-    const int per = 1 + a.n_stab, k = id - n_mi;
+    const int per = a.n_ent + a.n_stab, k = id - n_mi;
     *layer = k / per;
     *g = a.G + (k - *layer * per);
   }
@@ -204,7 +217,8 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   float* scal = a.scal + (size_t)layer * a.sc;
 
-  if (g == a.G) {   // ------------------------------------ entropy block
+  const int part = g == a.G ? 0 : g - a.G - a.n_stab;   // entropy part, if >= 1 (or block G)
+  if (g == a.G || part >= 1) {   // ----------------------- entropy blocks
     const float* sb = a.sbar + (size_t)layer * a.Lp;
     double z = 0.0;
     float vmax = 0.f;     // s-bar is non-negative
@@ -240,27 +254,34 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
       }
       return;
     }
+    // this block's part of the tokens
+    const double inv = 1.0 / denom;
+    const int each = (a.Lp + a.n_ent - 1) / a.n_ent;
+    const int t_end = min(a.Lp, (part + 1) * each);
     double e = 0.0;
-    for (int t0 = tid; t0 < a.Lp; t0 += kBatch * kThreads) {
+    for (int t0 = part * each + tid; t0 < t_end; t0 += kBatch * kThreads) {
       float v[kBatch];
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
         const int t = t0 + u * kThreads;
-        v[u] = t < a.Lp ? sb[t] : -1.f;
+        v[u] = t < t_end ? sb[t] : -1.f;
       }
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
         if (v[u] >= 0.f) {
-          const double p = (double)v[u] / denom;
+          const double p = (double)v[u] * inv;
           e += p * log(p + (double)a.eps);
         }
       }
     }
     e = block_sum_d(e, red);
     if (tid == 0) {
-      double h = 0.0;
-      if (a.Lp > 1) h = fmin(1.0, fmax(0.0, -e / log((double)a.Lp)));
-      scal[STARKV_SCAL_HHAT(a.G)] = (float)h;
+      if (a.n_ent > 1) {
+        // added up in block order by the layer's finalize
+        reinterpret_cast<StateHeader*>(a.state + (size_t)layer * a.state_stride)->ent[part] = e;
+      } else {
+        scal[STARKV_SCAL_HHAT(a.G)] = entropy_stat(e, a.Lp);
+      }
     }
     return;
   }
@@ -376,6 +397,9 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
     }
     if (tid == 0) sp_off[a.sp.n] = N;
     __syncthreads();
+    const bool dense = a.sp.dense, same = a.sp.same;
+    const int base = a.sp.start[0], frame = a.sp.off[1];
+    const int step = kThreads % frame;   // kThreads positions on, modulo the frame
     // Visual index i (ascending per thread) -> its span, by a cursor s.
     auto span_of = [&](int s, int i) {
       while (sp_off[s + 1] <= i) ++s;
@@ -400,7 +424,7 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
 #pragma unroll
       for (int u = 0; u < kKeyBatch; ++u) {
         const int i = i0 + u * kThreads;
-        v[u] = i < N ? Sg[token_of(i)] : 0.f;
+        v[u] = i < N ? Sg[dense ? base + i : token_of(i)] : 0.f;
       }
 #pragma unroll
       for (int u = 0; u < kKeyBatch; ++u) kv[u] = i0 + u * kThreads < N ? fkey(v[u]) : 0u;
@@ -467,7 +491,7 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
 #pragma unroll
         for (int u = 0; u < kLoadBatch; ++u) {
           const int i = i0 + u * kThreads;
-          v[u] = i < N ? Sg[token_of(i)] : 0.f;
+          v[u] = i < N ? Sg[dense ? base + i : token_of(i)] : 0.f;
         }
 #pragma unroll
         for (int u = 0; u < kLoadBatch; ++u) {
@@ -675,7 +699,7 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
             seg_dg[slot] = dg;
             seg_off[slot] = inc - cnt;
             seg_cnt[slot] = cnt;
-            seg_cur[slot] = 0;
+            seg_cur[slot] = inc - cnt;   // the next free slot
           }
           if (lane == 63) { cand_total = inc; n_seg = slot + 1; }
         }
@@ -690,34 +714,85 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
           f_nb = nb;
           jh = hist + kJointOff;
           for (int i = tid; i < K * ncell; i += kThreads) jh[i] = 0;
+          // Neighbouring tokens share cells and bins, so a wave's adds pile
+          // up on few counters: up to eight copies of the histogram, lane by
+          // lane, each starting nine banks after the one before (with a few
+          // keys per thread, adding them up costs more).  The wide
+          // shape has room behind the histogram, the others behind the table
+          // below (in digit histograms not needed before the copies are
+          // added up).
+          const int cells = K * ncell, cstride = cells + 9;
+          int* const extra = NT == 1024 ? jh + cells + 9 : hist + kFirstDigitBins / 2;
+          const int room = NT == 1024 ? kHistInts - kJointOff - cells - 9 : kFirstDigitBins / 2;
+          const int fit = N >= 4 * kThreads ? room / cstride : 0;
+          const int ncopy = fit >= 7 ? 8 : fit >= 3 ? 4 : fit >= 1 ? 2 : 1;
+          const int copy = lane & (ncopy - 1);
+          int* const jl = copy == 0 ? jh : extra + (copy - 1) * cstride;
 #pragma unroll
           for (int j = 0; j < 8; ++j)
             eb[j] = j < n_t ? ((t_key[j] >> shift) & (uint32_t)(nb - 1)) : 0xFFFFFFFFu;
           // per first-digit bucket, in the digit histogram's place (read
           // by the scan above, not needed again before the next digit): the
           // number of edges in lower buckets, i.e. the bin of a key outside
-          // the edges' buckets, with bit 8 set for an edge's own bucket
-          // (bins < 64)
-          int* const d_lut = hist;
-          for (int dd = tid; dd < nb; dd += kThreads)
-            d_lut[dd] = lower_edges((uint32_t)dd) |
-                        (int)(((bucket_bits[dd >> 5] >> (dd & 31)) & 1u) << 8);
-          __syncthreads();
-          fetch_reset();
-          auto fuse_key_in = [&](int i, uint32_t key, int cell) {
-            const uint32_t d = (key >> shift) & (uint32_t)(nb - 1);
-            const int lut = d_lut[d];
-            if (lut & 0x100) {
-              const int sg = seg_of_bucket(d);
-              const int pos = seg_off[sg] + atomicAdd(&seg_cur[sg], 1);
-              ck[pos] = key;
-              cv[pos] = ((uint32_t)cell << 24) | (uint32_t)i;
-            } else {
-              atomicAdd(&jh[lut * ncell + cell], 1);
+          // the edges' buckets (bins < 64), or for an edge's own bucket bit 8
+          // and its candidate segment above that
+          uint16_t* const d_lut = reinterpret_cast<uint16_t*>(hist);
+          for (int dd = tid; dd < nb; dd += kThreads) {
+            const bool edge = (bucket_bits[dd >> 5] >> (dd & 31)) & 1u;
+            d_lut[dd] = (uint16_t)(edge ? 0x100 | (seg_of_bucket((uint32_t)dd) << 9)
+                                        : lower_edges((uint32_t)dd));
+          }
+          for (int i = tid; i < (ncopy - 1) * cstride; i += kThreads) extra[i] = 0;
+          // Cells of a frame's tokens, a byte each, when every span has the
+          // same shape and the table fits: behind the histogram's copies in
+          // the wide shape; else, with uncached keys, in the candidate area
+          // (the key cache then holds the candidates).
+          uint8_t* const cell_tab =
+              reinterpret_cast<uint8_t*>(NT == 1024 ? extra + (ncopy - 1) * cstride
+                                                    : reinterpret_cast<int*>(cand));
+          const int tab_bytes = NT == 1024 ? 4 * (room - (ncopy - 1) * cstride)
+                                           : (cached ? 0 : 4 * kCand);
+          const bool tabled = same && a.sp.n > 1 && frame <= tab_bytes;
+          if (tabled) {
+            const float rc = __builtin_amdgcn_rcpf((float)sp_cols[0]);
+            const float fr = (float)M * __builtin_amdgcn_rcpf((float)sp_rows[0]);
+            const float fc = (float)M * rc;
+            for (int p = tid; p < frame; p += kThreads) {
+              int r, c;
+              span_row_col(p, sp_cols[0], &r, &c);
+              cell_tab[p] = (uint8_t)grid_cell(r, c, sp_rows[0], sp_cols[0], M, fr, fc);
             }
+          }
+          __syncthreads();
+          // kFuse keys of a thread at a time (visual indices i0 + u *
+          // kThreads, the first n valid): all their table reads, then all
+          // their histogram adds and slot requests, then the candidates'
+          // writes, so that a step's LDS latencies overlap instead of
+          // adding up.  One key at a time, with a search for its segment and
+          // its cell computed from the index, this pass took 98 us at 139,230
+          // keys per subspace (4 on 28 layers), 31 us at 13,455 (28 on 28
+          // layers) and 8.9 us at 13,455 (4 on 28 layers, keys in LDS); now
+          // 46, 23 and 7.0.  Reading S bounds the first of them: a CU gets
+          // about 25 bytes a ns, each pass over the keys 22 us.
+          auto fuse = [&](int i0, int n, const uint32_t (&kv)[kFuse], const int (&cell)[kFuse]) {
+            int lut[kFuse], pos[kFuse];
+#pragma unroll
+            for (int u = 0; u < kFuse; ++u)
+              lut[u] = d_lut[(kv[u] >> shift) & (uint32_t)(nb - 1)];
+#pragma unroll
+            for (int u = 0; u < kFuse; ++u)
+              if (u < n && !(lut[u] & 0x100)) atomicAdd(&jl[lut[u] * ncell + cell[u]], 1);
+#pragma unroll
+            for (int u = 0; u < kFuse; ++u)
+              if (u < n && (lut[u] & 0x100)) pos[u] = atomicAdd(&seg_cur[lut[u] >> 9], 1);
+#pragma unroll
+            for (int u = 0; u < kFuse; ++u)
+              if (u < n && (lut[u] & 0x100)) {
+                ck[pos[u]] = kv[u];
+                cv[pos[u]] = ((uint32_t)cell[u] << 24) | (uint32_t)(i0 + u * kThreads);
+              }
           };
-          cell_reset();
-          if (cached) {
+          if (cached && !tabled) {
             // keys in LDS: span by span, so that the span's constants are
             // uniform and a thread's (row, col) only steps inside the span
             for (int sp = 0; sp < a.sp.n; ++sp) {
@@ -728,27 +803,79 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
               const int dq = small_quot(kThreads, cols, rc), dr = kThreads - dq * cols;
               int r = small_quot(tid, cols, rc);
               int c = tid - r * cols;
-#pragma unroll 2
-              for (int i = a.sp.off[sp] + tid; i < end; i += kThreads) {
-                fuse_key_in(i, kc[i], grid_cell(r, c, rows, cols, M, fr, fc));
-                c += dr;
-                r += dq;
-                if (c >= cols) { c -= cols; ++r; }
+              for (int i0 = a.sp.off[sp] + tid; i0 < end; i0 += kFuse * kThreads) {
+                uint32_t kv[kFuse];
+                int cell[kFuse];
+#pragma unroll
+                for (int u = 0; u < kFuse; ++u) {
+                  const int i = i0 + u * kThreads;
+                  kv[u] = 0u;
+                  cell[u] = 0;
+                  if (i < end) {
+                    kv[u] = kc[i];
+                    cell[u] = grid_cell(r, c, rows, cols, M, fr, fc);
+                    c += dr;
+                    r += dq;
+                    if (c >= cols) { c -= cols; ++r; }
+                  }
+                }
+                fuse(i0, (end - i0 + kThreads - 1) / kThreads, kv, cell);
               }
             }
-          } else {        // kKeyBatch loads in flight
+          } else {        // cached: keys in LDS; else kSub * kFuse loads in flight
+            constexpr int kSub = 2;
             fetch_reset();
-            for (int i0 = tid; i0 < N; i0 += kKeyBatch * kThreads) {
-              uint32_t kv[kKeyBatch];
-              fetch(i0, kv);
+            cell_reset();
+            int p = tid;
+            while (tabled && p >= frame) p -= frame;
+            for (int i0 = tid; i0 < N; i0 += kSub * kFuse * kThreads) {
+              uint32_t kw[kSub * kFuse];
+              if (cached) {
 #pragma unroll
-              for (int u = 0; u < kKeyBatch; ++u) {
-                const int i = i0 + u * kThreads;
-                if (i < N) fuse_key_in(i, kv[u], cell_at(i));
+                for (int u = 0; u < kSub * kFuse; ++u)
+                  kw[u] = i0 + u * kThreads < N ? kc[i0 + u * kThreads] : 0u;
+              } else {
+                float v[kSub * kFuse];
+#pragma unroll
+                for (int u = 0; u < kSub * kFuse; ++u) {
+                  const int i = i0 + u * kThreads;
+                  v[u] = i < N ? Sg[dense ? base + i : token_of(i)] : 0.f;
+                }
+#pragma unroll
+                for (int u = 0; u < kSub * kFuse; ++u) kw[u] = fkey(v[u]);
+              }
+#pragma unroll
+              for (int w = 0; w < kSub; ++w) {
+                const int j0 = i0 + w * kFuse * kThreads;
+                if (j0 >= N) break;
+                uint32_t kv[kFuse];
+                int cell[kFuse];
+#pragma unroll
+                for (int u = 0; u < kFuse; ++u) {
+                  const int i = j0 + u * kThreads;
+                  kv[u] = kw[w * kFuse + u];
+                  cell[u] = 0;
+                  if (tabled) {
+                    cell[u] = cell_tab[p];
+                    p += step;
+                    if (p >= frame) p -= frame;
+                  } else if (i < N) {
+                    cell[u] = cell_at(i);
+                  }
+                }
+                fuse(j0, (N - j0 + kThreads - 1) / kThreads, kv, cell);
               }
             }
           }
           __syncthreads();
+          if (ncopy > 1) {
+            for (int i = tid; i < cells; i += kThreads) {
+              int n = jh[i];
+              for (int c = 0; c < ncopy - 1; ++c) n += extra[c * cstride + i];
+              jh[i] = n;
+            }
+            __syncthreads();
+          }
           compact = true;
           n_c = cand_total;
           if (n_c <= kDirect) {
@@ -767,7 +894,7 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
               const uint32_t dg = (kv[u] >> shift) & (uint32_t)(nb - 1);
               if (i0 + u * kThreads < N && ((bucket_bits[dg >> 5] >> (dg & 31)) & 1u)) {
                 const int sg = seg_of_bucket(dg);
-                ck[seg_off[sg] + atomicAdd(&seg_cur[sg], 1)] = kv[u];
+                ck[atomicAdd(&seg_cur[sg], 1)] = kv[u];
               }
             }
           }
@@ -1011,7 +1138,18 @@ __device__ __forceinline__ void finalize_layer(const FinalArgs& a, int layer, in
   const int G = a.G;
   const bool on = lane < G;
   const int n_prev = hdr->n;
-  const float h = scal[STARKV_SCAL_HHAT(G)];
+  float h;
+  if (a.n_ent > 1) {
+    double e = 0.0;
+    for (int i = 0; i < a.n_ent; ++i) e += hdr->ent[i];
+    h = entropy_stat(e, a.Lp);
+    if (lane == 0) {
+      scal[STARKV_SCAL_HHAT(G)] = h;
+      for (int i = 0; i < a.n_ent; ++i) hdr->ent[i] = 0.0;
+    }
+  } else {
+    h = scal[STARKV_SCAL_HHAT(G)];
+  }
   double v = 0.0;
   if (on) {
     v = (double)a.rho_mi * (double)mibar[lane] +
@@ -1058,7 +1196,7 @@ __device__ __forceinline__ void finalize_layer(const FinalArgs& a, int layer, in
 // selection (select_body) in the same workgroup, its LDS carved from the
 // statistics' dynamic LDS, which no longer holds anything live by then.
 template <int NT, bool SEL>
-__global__ __launch_bounds__(NT, 1024 / NT) void stats_kernel(StatsArgs a, SelArgs sel) {
+__global__ __launch_bounds__(NT, NT == 1024 ? 1 : 4) void stats_kernel(StatsArgs a, SelArgs sel) {
   static_assert(!SEL || NT == kSelThreads, "the selection body needs a 1024-thread block");
   __shared__ int last_s;
   int layer, g;
@@ -1083,7 +1221,7 @@ __global__ __launch_bounds__(NT, 1024 / NT) void stats_kernel(StatsArgs a, SelAr
     __syncthreads();
     if (threadIdx.x == 0) {
       __threadfence();
-      last_s = atomicAdd(&hdr->arrive, 1) == a.G + a.n_stab;
+      last_s = atomicAdd(&hdr->arrive, 1) == a.G + a.n_ent + a.n_stab - 1;
     }
     __syncthreads();
     if (!last_s) return;
@@ -1136,18 +1274,23 @@ StatsArgs make_stats_args(const Geometry& g, const starkv_params& p, const float
   a.frame_cap = frame_cap;
   a.sc = (int)scalars_count(g.Ns);
   a.n_stab = stats_stab_blocks(g.Ns);
+  a.n_ent = stats_entropy_blocks(g.Lp, p.aeb_mode == STARKV_AEB_ENTROPY);
   a.n_layers = g.n_layers;
   a.aeb = p.aeb_mode;
   a.rho_t = p.rho_t;
   a.eps = p.eps;
   a.sp.n = n_spans;
   a.sp.off[0] = 0;
+  a.sp.dense = a.sp.same = 0;
   for (int i = 0; i < n_spans; ++i) {
     a.sp.start[i] = spans[i].start;
     a.sp.rows[i] = spans[i].rows;
     a.sp.cols[i] = spans[i].cols;
     a.sp.frame[i] = spans[i].frame;
     a.sp.off[i + 1] = a.sp.off[i] + spans[i].rows * spans[i].cols;
+    a.sp.dense = (i == 0 || a.sp.dense) && spans[i].start - a.sp.off[i] == spans[0].start;
+    a.sp.same = (i == 0 || a.sp.same) && spans[i].rows == spans[0].rows &&
+                spans[i].cols == spans[0].cols;
   }
   FinalArgs& f = a.fin;
   f.scal = scalars;
@@ -1155,6 +1298,8 @@ StatsArgs make_stats_args(const Geometry& g, const starkv_params& p, const float
   f.state_stride = a.state_stride;
   f.G = g.Ns;
   f.sc = a.sc;
+  f.n_ent = a.n_ent;
+  f.Lp = g.Lp;
   f.nf = a.cur >= 0 ? spans[a.cur].rows * spans[a.cur].cols : -1;
   f.rho_mi = p.rho_mi;
   f.tau = p.tau;
@@ -1204,7 +1349,7 @@ int launch_update_state(const Geometry& g, const starkv_params& p,
   set_wide_lds_attributes();
   const int nt = stats_shape(g, p);
   if (nt < 0) return (int)hipErrorInvalidDevice;
-  const dim3 grid(stats_layer_blocks(g.Ns) * g.n_layers);
+  const dim3 grid((stats_layer_blocks(g.Ns) + a.n_ent - 1) * g.n_layers);
   SelArgs none{};
   if (nt == 256)
     stats_kernel<256, false><<<grid, 256, stats_lds<256>(), st>>>(a, none);
@@ -1237,8 +1382,8 @@ int launch_update_state_select(const Geometry& g, const starkv_params& p, const 
   fill_sel_args(sel, g, p, sbar, gstar, scalars, spans, n_spans, frame, B, s, idx,
                 (int)std::min<long>({(long)g.Lp, (long)kSelLdsKeys, room}));
   set_wide_lds_attributes();
-  stats_kernel<1024, true><<<stats_layer_blocks(g.Ns) * g.n_layers, 1024, stats_lds<1024>(),
-                             st>>>(a, sel);
+  stats_kernel<1024, true><<<(stats_layer_blocks(g.Ns) + a.n_ent - 1) * g.n_layers, 1024,
+                             stats_lds<1024>(), st>>>(a, sel);
   return (int)hipGetLastError();
 }
 

@@ -318,3 +318,66 @@ def test_sixty_four_spans(mixed):
         p = sk.params_default()
         p.n_bins, p.grid = K, M
         run_stats(f"64 spans mixed={mixed} K{K} M{M}", steps, sbar, spans, 64, p)
+
+
+# (frames, rows, cols, gap, per_head, n_bins, grid): the fused binning pass's
+# forms: few keys (one histogram) and many (copies), spans of one shape (cell
+# table) or not, adjacent spans (no cursor) or gaps, cached and uncached keys,
+# every block shape, and the entropy sum split over blocks
+FUSED_FORMS = [
+    (1, 39, 69, 0, False, 8, 8), (2, 46, 46, 0, False, 8, 8), (5, 39, 69, 0, False, 8, 8),
+    (5, 39, 69, 3, False, 8, 8), (12, 51, 91, 0, False, 8, 8), (12, 51, 91, 5, False, 8, 8),
+    (8, 51, 91, -1, False, 8, 8), (3, 97, 90, 0, False, 16, 16), (5, 39, 69, 0, True, 8, 8),
+    (5, 39, 69, 2, True, 12, 8), (4, 65, 64, 0, True, 9, 8), (2, 600, 40, 0, False, 8, 8),
+]
+
+
+@pytest.mark.parametrize("form", FUSED_FORMS, ids=["-".join(map(str, f)) for f in FUSED_FORMS])
+def test_fused_binning_forms(form):
+    """MI of every form against a stable-sort ranking in 64 bits; counts are
+    whole numbers, so only the final logarithms round: 1e-6 of log(n_bins)."""
+    import math
+    import torch
+    from paper_2606_01790_amd import starkv as sk
+    frames, rows, cols, gap, per_head, n_bins, grid = form
+    nl, H, G, W = 28 if per_head else 3, 28 if per_head else 4, 4, 32
+    spans, t = [], 7
+    for f in range(frames):
+        r = rows - 2 * (f % 3) if gap < 0 else rows    # gap -1: shapes differ
+        spans.append((t, r, cols, f + 1))
+        t += r * cols + max(gap, 0) * (f % 2)
+    Lp = t + 50
+    dims = sk.make_dims(nl, H, G, 128, Lp + W, W, sk.BF16, per_head)
+    p = sk.params_default()
+    p.n_bins, p.grid = n_bins, grid
+    g = torch.Generator(device="cuda").manual_seed(sum(form[:3]))
+    Ns = dims.Ns
+    S = torch.exp(0.4 * torch.randn(nl, Ns, Lp, generator=g, device="cuda"))
+    S[:, :, ::3] = S[:, :, ::3].half().float()          # some ties
+    sbar = S.mean(1).contiguous()
+    nf = max(s[1] * s[2] for s in spans)
+    state = torch.zeros(sk.state_bytes(dims, nf), dtype=torch.uint8, device="cuda")
+    sk.state_init(dims, state, nf)
+    scal = torch.empty(nl, sk.scalars_count(dims), device="cuda")
+    sk.update_state(dims, p, S, sbar, spans, frames, state, nf, scal)
+    torch.cuda.synchronize()
+    pos = torch.cat([torch.arange(s[0], s[0] + s[1] * s[2]) for s in spans]).cuda()
+    cell = torch.cat([(torch.arange(s[1] * s[2]) // s[2] * grid // s[1]) * grid +
+                      torch.arange(s[1] * s[2]) % s[2] * grid // s[2] for s in spans]).cuda()
+    N = pos.numel()
+    order = S[:, :, pos].sort(dim=2, stable=True).indices
+    bins = torch.empty_like(order)
+    bins.scatter_(2, order, (torch.arange(N, device="cuda") * n_bins // N).expand_as(order).contiguous())
+    joint = torch.zeros(nl, Ns, n_bins * grid * grid, dtype=torch.float64, device="cuda")
+    joint.scatter_add_(2, bins * (grid * grid) + cell, torch.ones_like(bins, dtype=torch.float64))
+    P = joint.view(nl, Ns, n_bins, grid * grid) / N
+    ind = P.sum(3, keepdim=True) * P.sum(2, keepdim=True)
+    mi = torch.where(P > 0, P * torch.log(P / ind.clamp_min(1e-300)), 0.0).sum((2, 3))
+    err = (scal[:, :Ns].double() - mi).abs().max()
+    assert float(err) <= 1e-6 * math.log(max(n_bins, 2)), float(err)
+    q = sbar.double() / (sbar.double().sum(1, keepdim=True) + p.eps)
+    h = -(q * torch.log(q + p.eps)).sum(1) / math.log(Lp)
+    assert float((scal[:, 4 * Ns + 1].double() - h).abs().max()) <= 2.0 ** -23
+    # the header's running sums and count are cleared for the next update
+    head = state.view(nl, -1)[:, 20:64]
+    assert int(head.count_nonzero()) == 0
