@@ -82,11 +82,14 @@ STARKV_HD inline int slab_chunks(const SlabGrid& g, int lg) {
 // slabs to whole rounds, every block its start.  Equal ranges win when the
 // slabs are many rounds per CU, aligned blocks when they are few (28 layers
 // of 4 groups: aligned at one 1920x1080 frame, 30.0 us against 35.6 in pass
-// 1 and 26.2 against 28.1 in pass 2; equal ranges at 30 frames).  In
-// between they tie to within 5% either way and aligned blocks are taken.
+// 1 and 26.2 against 28.1 in pass 2; equal ranges at 30 frames).  At a tie
+// (five frames) pass 2 takes equal ranges, 106 us against 111, and pass 1,
+// whose every segment starts with a reference slab, aligned blocks, 108 us
+// against 113.
 // With at most four slabs in a block, several waves share a slab, each with
 // its part of the row blocks.
-inline SlabLaunch slab_grid(int Lp, int nlg, int nrb, int n_cu, int max_per_lg, bool share) {
+inline SlabLaunch slab_grid(int Lp, int nlg, int nrb, int n_cu, int max_per_lg, bool share,
+                            bool equal) {
   SlabLaunch l;
   SlabGrid& g = l.g;
   g.S = (Lp + kSlab - 1) / kSlab;
@@ -121,7 +124,7 @@ inline SlabLaunch slab_grid(int Lp, int nlg, int nrb, int n_cu, int max_per_lg, 
     const int64_t segs = (q + g.S - 2) / g.S + 1;
     const int64_t chunks = (g.S + q_min - 2) / q_min + 1;   // blocks per group at most
     const int64_t cost = (q + kSlabWaves - 1) / kSlabWaves * 8 + kStart + (segs - 1) * (8 + kStart);
-    if (chunks <= max_per_lg && cost < best) {
+    if (chunks <= max_per_lg && (equal ? cost <= best : cost < best)) {
       g.per_lg = 0;
       g.q = (int)q_min;
       g.r = (int)(total - q_min * n_cu);
@@ -147,8 +150,8 @@ inline SlabLaunch slab_grid(int Lp, int nlg, int nrb, int n_cu, int max_per_lg, 
 // pass 2 at 184 blocks 6.1 / 7.9, 368 blocks 8.8 / 9.3, 528 blocks 11.1 / 9.8.
 inline void slab_launches(int Lp, int nlg, int nrb, int n_cu, int max_chunks, bool one_sum,
                           bool whole_blocks, SlabLaunch* p1, SlabLaunch* p2) {
-  *p1 = slab_grid(Lp, nlg, nrb, n_cu, max_chunks, true);
-  *p2 = slab_grid(Lp, nlg, nrb, n_cu, 1 << 30, one_sum);
+  *p1 = slab_grid(Lp, nlg, nrb, n_cu, max_chunks, true, false);
+  *p2 = slab_grid(Lp, nlg, nrb, n_cu, 1 << 30, one_sum, true);
   if (nrb > kSmallWaves) return;
   const int64_t chunks = (Lp + kSmallRows - 1) / kSmallRows;
   if (chunks <= max_chunks && chunks * nlg <= n_cu) {
