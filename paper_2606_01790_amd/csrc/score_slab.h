@@ -67,8 +67,8 @@ constexpr int kSlabThreads = kSlabWaves * 64;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegBig = -1e30f;
 // A block's sum against its reference stays below this unless a logit rises
-// 64 log2 units above the block's first slab; then the row statistics are
-// redone against exact running maxima.
+// about 64 log2 units above the reference slab; then the block's row
+// statistics are redone against exact running maxima.
 constexpr float kSumLimit = 18446744073709551616.0f;   // 2^64
 
 // Pass-2 output: one sum per group; one per head, a head being whole row
@@ -348,10 +348,10 @@ __device__ __forceinline__ float tile_sum2(const f32x16& acc, float scale, const
   return s[0] + s[1];
 }
 
-// Waits for every load of the wave.  Called where only the next slab's K is
-// outstanding, a whole slab after its issue: a loop that uses registers
-// whose loads may (as far as the compiler can tell) be outstanding would
-// wait for the newer loads behind them too.
+// Waits for every load of the wave, at the end of a step whose other register
+// set was loaded meanwhile: a loop that uses registers whose loads may (as
+// far as the compiler can tell) be outstanding would wait for the newer
+// loads behind them too.
 __device__ __forceinline__ void loads_landed() {
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
 }
