@@ -182,7 +182,8 @@ __device__ __forceinline__ void stats_block(const StatsArgs& a, int* layer, int*
   }
 }
 
-template <int NT>
+// CACHED: the visual keys fit the block shape's key cache.
+template <int NT, bool CACHED>
 __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g) {
   constexpr int kThreads = NT, kWaves = NT / 64;
   constexpr int kHistInts = StatsShape<NT>::kHistInts, kKeyCache = StatsShape<NT>::kKeyCache,
@@ -370,7 +371,7 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
   const int K = a.nbins;
   const int M = a.grid;
   const int ncell = M * M;
-  const bool cached = N <= kKeyCache;
+  constexpr bool cached = CACHED;   // N <= kKeyCache
   // Candidates (keys in the edges' first-digit buckets): the fused pass
   // keeps (key, cell << 24 | visual index) pairs, the compaction pass keys
   // only; in the candidate area while the keys are cached, else in the key
@@ -397,16 +398,14 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
     }
     if (tid == 0) sp_off[a.sp.n] = N;
     __syncthreads();
-    const bool dense = a.sp.dense, same = a.sp.same;
-    const int base = a.sp.start[0], frame = a.sp.off[1];
-    const int step = kThreads % frame;   // kThreads positions on, modulo the frame
     // Visual index i (ascending per thread) -> its span, by a cursor s.
     auto span_of = [&](int s, int i) {
       while (sp_off[s + 1] <= i) ++s;
       return s;
     };
     // Token positions of a thread's visual indices (ascending): the span
-    // cursor keeps the current span's end and its token - index offset.
+    // cursor keeps the current span's end and its token - index offset
+    // (adjacent spans count as one).
     int f_s = 0, f_end = 0, f_base = 0;
     auto token_of = [&](int i) {
       if (i >= f_end) {
@@ -416,7 +415,11 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
       }
       return f_base + i;
     };
-    auto fetch_reset = [&]() { f_s = 0; f_end = 0; };
+    auto fetch_reset = [&]() {
+      f_s = 0;
+      f_end = a.sp.dense ? N : 0;
+      f_base = a.sp.start[0];
+    };
     // The kKeyBatch keys i0 + u * kThreads of this thread (0 past N), read
     // from S with kKeyBatch loads in flight.
     auto fetch = [&](int i0, uint32_t (&kv)[kKeyBatch]) {
@@ -424,7 +427,7 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
 #pragma unroll
       for (int u = 0; u < kKeyBatch; ++u) {
         const int i = i0 + u * kThreads;
-        v[u] = i < N ? Sg[dense ? base + i : token_of(i)] : 0.f;
+        v[u] = i < N ? Sg[token_of(i)] : 0.f;
       }
 #pragma unroll
       for (int u = 0; u < kKeyBatch; ++u) kv[u] = i0 + u * kThreads < N ? fkey(v[u]) : 0u;
@@ -491,7 +494,7 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
 #pragma unroll
         for (int u = 0; u < kLoadBatch; ++u) {
           const int i = i0 + u * kThreads;
-          v[u] = i < N ? Sg[dense ? base + i : token_of(i)] : 0.f;
+          v[u] = i < N ? Sg[token_of(i)] : 0.f;
         }
 #pragma unroll
         for (int u = 0; u < kLoadBatch; ++u) {
@@ -752,7 +755,8 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
                                                     : reinterpret_cast<int*>(cand));
           const int tab_bytes = NT == 1024 ? 4 * (room - (ncopy - 1) * cstride)
                                            : (cached ? 0 : 4 * kCand);
-          const bool tabled = same && a.sp.n > 1 && frame <= tab_bytes;
+          const int frame = a.sp.off[1];
+          const bool tabled = a.sp.same && a.sp.n > 1 && frame <= tab_bytes;
           if (tabled) {
             const float rc = __builtin_amdgcn_rcpf((float)sp_cols[0]);
             const float fr = (float)M * __builtin_amdgcn_rcpf((float)sp_rows[0]);
@@ -824,12 +828,7 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
             }
           } else {        // cached: keys in LDS; else kSub * kFuse loads in flight
             constexpr int kSub = 2;
-            fetch_reset();
-            cell_reset();
-            int p = tid;
-            while (tabled && p >= frame) p -= frame;
-            for (int i0 = tid; i0 < N; i0 += kSub * kFuse * kThreads) {
-              uint32_t kw[kSub * kFuse];
+            auto load = [&](int i0, uint32_t (&kw)[kSub * kFuse]) {
               if (cached) {
 #pragma unroll
                 for (int u = 0; u < kSub * kFuse; ++u)
@@ -839,32 +838,45 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
 #pragma unroll
                 for (int u = 0; u < kSub * kFuse; ++u) {
                   const int i = i0 + u * kThreads;
-                  v[u] = i < N ? Sg[dense ? base + i : token_of(i)] : 0.f;
+                  v[u] = i < N ? Sg[token_of(i)] : 0.f;
                 }
 #pragma unroll
                 for (int u = 0; u < kSub * kFuse; ++u) kw[u] = fkey(v[u]);
               }
+            };
+            // cell_of(i): the cells of this thread's indices, in order
+            auto walk = [&](auto cell_of) {
+              for (int i0 = tid; i0 < N; i0 += kSub * kFuse * kThreads) {
+                uint32_t kw[kSub * kFuse];
+                load(i0, kw);
 #pragma unroll
-              for (int w = 0; w < kSub; ++w) {
-                const int j0 = i0 + w * kFuse * kThreads;
-                if (j0 >= N) break;
-                uint32_t kv[kFuse];
-                int cell[kFuse];
+                for (int w = 0; w < kSub; ++w) {
+                  const int j0 = i0 + w * kFuse * kThreads;
+                  if (j0 >= N) break;
+                  uint32_t kv[kFuse];
+                  int cell[kFuse];
 #pragma unroll
-                for (int u = 0; u < kFuse; ++u) {
-                  const int i = j0 + u * kThreads;
-                  kv[u] = kw[w * kFuse + u];
-                  cell[u] = 0;
-                  if (tabled) {
-                    cell[u] = cell_tab[p];
-                    p += step;
-                    if (p >= frame) p -= frame;
-                  } else if (i < N) {
-                    cell[u] = cell_at(i);
+                  for (int u = 0; u < kFuse; ++u) {
+                    kv[u] = kw[w * kFuse + u];
+                    cell[u] = cell_of(j0 + u * kThreads);
                   }
+                  fuse(j0, (N - j0 + kThreads - 1) / kThreads, kv, cell);
                 }
-                fuse(j0, (N - j0 + kThreads - 1) / kThreads, kv, cell);
               }
+            };
+            fetch_reset();
+            if (tabled) {
+              const int step = kThreads % frame;   // kThreads positions on, modulo the frame
+              int p = tid % frame;
+              walk([&](int) {
+                const int cell = cell_tab[p];
+                p += step;
+                if (p >= frame) p -= frame;
+                return cell;
+              });
+            } else {
+              cell_reset();
+              walk([&](int i) { return i < N ? cell_at(i) : 0; });
             }
           }
           __syncthreads();
@@ -1195,7 +1207,7 @@ __device__ __forceinline__ void finalize_layer(const FinalArgs& a, int layer, in
 // With SEL, the block that runs a layer's finalize then runs that layer's
 // selection (select_body) in the same workgroup, its LDS carved from the
 // statistics' dynamic LDS, which no longer holds anything live by then.
-template <int NT, bool SEL>
+template <int NT, bool SEL, bool CACHED>
 __global__ __launch_bounds__(NT, NT == 1024 ? 1 : 4) void stats_kernel(StatsArgs a, SelArgs sel) {
   static_assert(!SEL || NT == kSelThreads, "the selection body needs a 1024-thread block");
   __shared__ int last_s;
@@ -1213,7 +1225,7 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 1 : 4) void stats_kernel(StatsArgs
     for (int i = threadIdx.x; i < a.sc; i += NT)
       a.scal[(size_t)layer * a.sc + i] = __builtin_nanf("");
   } else {
-    stats_body<NT>(a, layer, g);
+    stats_body<NT, CACHED>(a, layer, g);
     // Lanes of wave 0 wrote every value the finalize and a fused selection
     // read from this block (MI_g or H^ by thread 0, phi by the first four
     // lanes); thread 0's fence, in that wave, publishes them before it
@@ -1312,17 +1324,41 @@ StatsArgs make_stats_args(const Geometry& g, const starkv_params& p, const float
   return a;
 }
 
-// The wide shape's dynamic LDS is above the default limit; raised once per
-// process (function-local static initialisation is thread-safe).
-void set_wide_lds_attributes() {
-  static const hipError_t attr_plain = hipFuncSetAttribute(
-      reinterpret_cast<const void*>(&stats_kernel<1024, false>),
-      hipFuncAttributeMaxDynamicSharedMemorySize, (int)stats_lds<1024>());
-  static const hipError_t attr_sel = hipFuncSetAttribute(
-      reinterpret_cast<const void*>(&stats_kernel<1024, true>),
-      hipFuncAttributeMaxDynamicSharedMemorySize, (int)stats_lds<1024>());
-  (void)attr_plain;
-  (void)attr_sel;
+template <int NT, bool SEL, bool CACHED>
+void raise_lds_limit() {
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&stats_kernel<NT, SEL, CACHED>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)stats_lds<NT>());
+}
+
+// The wide and narrow shapes' dynamic LDS is above the default limit; raised
+// once per process (function-local static initialisation is thread-safe).
+void raise_lds_limits() {
+  static const bool raised = [] {
+    raise_lds_limit<1024, true, true>();
+    raise_lds_limit<1024, true, false>();
+    raise_lds_limit<1024, false, true>();
+    raise_lds_limit<1024, false, false>();
+    raise_lds_limit<512, false, true>();
+    raise_lds_limit<512, false, false>();
+    return true;
+  }();
+  (void)raised;
+}
+
+// The keys are kept in LDS by one kernel and read from S in every pass by
+// another.  With both forms in one, calls of one frame paid for the other's
+// registers and instruction fetches: one frame of 28 layers of 4 groups 34.4
+// us against 34.0 apart, five frames 49.7 against 48.6, a subspace per head
+// at twelve frames 127 against 120.
+template <int NT, bool SEL>
+int launch_stats(const StatsArgs& a, const SelArgs& sel, hipStream_t st) {
+  raise_lds_limits();
+  const int blocks = (stats_layer_blocks(a.G) + a.n_ent - 1) * a.n_layers;
+  if (a.sp.off[a.sp.n] <= StatsShape<NT>::kKeyCache)
+    stats_kernel<NT, SEL, true><<<blocks, NT, stats_lds<NT>(), st>>>(a, sel);
+  else
+    stats_kernel<NT, SEL, false><<<blocks, NT, stats_lds<NT>(), st>>>(a, sel);
+  return (int)hipGetLastError();
 }
 
 // The statistics block shape for this call (stats_shape.h); -1 when the
@@ -1346,18 +1382,12 @@ int launch_update_state(const Geometry& g, const starkv_params& p,
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const StatsArgs a = make_stats_args(g, p, S, sbar, spans, n_spans, frame, state, frame_cap,
                                       scalars);
-  set_wide_lds_attributes();
   const int nt = stats_shape(g, p);
   if (nt < 0) return (int)hipErrorInvalidDevice;
-  const dim3 grid((stats_layer_blocks(g.Ns) + a.n_ent - 1) * g.n_layers);
   SelArgs none{};
-  if (nt == 256)
-    stats_kernel<256, false><<<grid, 256, stats_lds<256>(), st>>>(a, none);
-  else if (nt == 512)
-    stats_kernel<512, false><<<grid, 512, stats_lds<512>(), st>>>(a, none);
-  else
-    stats_kernel<1024, false><<<grid, 1024, stats_lds<1024>(), st>>>(a, none);
-  return (int)hipGetLastError();
+  if (nt == 256) return launch_stats<256, false>(a, none, st);
+  if (nt == 512) return launch_stats<512, false>(a, none, st);
+  return launch_stats<1024, false>(a, none, st);
 }
 
 int launch_update_state_select(const Geometry& g, const starkv_params& p, const float* S,
@@ -1381,10 +1411,7 @@ int launch_update_state_select(const Geometry& g, const starkv_params& p, const 
   const long room = (long)((stats_lds<1024>() - kSelKeysOff) / sizeof(uint32_t));
   fill_sel_args(sel, g, p, sbar, gstar, scalars, spans, n_spans, frame, B, s, idx,
                 (int)std::min<long>({(long)g.Lp, (long)kSelLdsKeys, room}));
-  set_wide_lds_attributes();
-  stats_kernel<1024, true><<<(stats_layer_blocks(g.Ns) + a.n_ent - 1) * g.n_layers, 1024,
-                             stats_lds<1024>(), st>>>(a, sel);
-  return (int)hipGetLastError();
+  return launch_stats<1024, true>(a, sel, st);
 }
 
 int launch_state_init(const Geometry& g, void* state, int32_t frame_cap, void* stream) {

@@ -77,6 +77,32 @@ def test_stats_kernel_lds_fits(tmp_path):
 
 
 @needs_hipcc
+def test_stats_kernels_use_no_scratch(tmp_path):
+    """Every form of the statistics kernel (three block shapes, with and
+    without the selection, visual keys in LDS or read from memory) keeps its
+    values in registers: scratch memory is set up and touched also by calls
+    whose own pass needs none of it.  Each form's LDS fits as above."""
+    path = os.path.join(B.CSRC, "state.hip")
+    src = open(path).read()
+    out = tmp_path / "state.s"
+    flags = [f for f in B.HIP_FLAGS if f != "-fPIC"]
+    subprocess.run([B.HIPCC, *flags, "-I", B.INCLUDE, "--cuda-device-only", "-S",
+                    "-o", str(out), path], check=True, capture_output=True)
+    seen = set()
+    for blk in out.read_text().split("amdhsa.kernels:", 1)[1].split("\n  - ")[1:]:
+        m = re.search(r"\.name:\s+\S*stats_kernelILi(\d+)(\S*)", blk)
+        if not m:
+            continue
+        field = lambda k: int(re.search(r"\.%s:\s+(\d+)" % k, blk).group(1))
+        nt = int(m.group(1))
+        seen.add((nt, m.group(2)))
+        assert field("private_segment_fixed_size") == 0, m.group(0)
+        lds = _shape(src, nt) + field("group_segment_fixed_size")
+        assert lds * (1024 // nt) <= LDS_LIMIT, (m.group(0), lds)
+    assert {nt for nt, _ in seen} == {256, 512, 1024}
+
+
+@needs_hipcc
 def test_select_kernel_lds_fits(tmp_path):
     path = os.path.join(B.CSRC, "select.hip")
     src = open(os.path.join(B.CSRC, "select_body.h")).read()

@@ -381,3 +381,18 @@ def test_fused_binning_forms(form):
     # the header's running sums and count are cleared for the next update
     head = state.view(nl, -1)[:, 20:64]
     assert int(head.count_nonzero()) == 0
+
+
+# visual tokens at the key cache's size and one past it, of the wide, the
+# narrow and the small block shape (the last two: a subspace per head)
+CACHE_EDGES = [
+    (1, 128, 160, 0, False, 8, 8), (1, 3, 6827, 0, False, 8, 8), (1, 64, 96, 0, True, 12, 8),
+    (1, 5, 1229, 0, True, 12, 8), (1, 32, 64, 0, True, 8, 8), (1, 3, 683, 0, True, 8, 8),
+]
+
+
+@pytest.mark.parametrize("form", CACHE_EDGES, ids=["-".join(map(str, f)) for f in CACHE_EDGES])
+def test_key_cache_edges(form):
+    """The kernel that keeps the keys in LDS and the one that reads them from
+    S, on both sides of every shape's limit."""
+    test_fused_binning_forms(form)
