@@ -77,23 +77,29 @@ STARKV_HD inline int slab_chunks(const SlabGrid& g, int lg) {
 // A pass's blocks (one per CU at a time: the window rows fill the LDS).
 // Either `per_lg` blocks per (layer, group), or one block per CU on equal
 // ranges that cross groups.  The unit of the estimate is an eighth of a
-// slab round, the time the block's eight waves take for a slab each; every
-// group a block touches costs its window rows and the rounding of its
-// slabs to whole rounds, every block its start.  Equal ranges win when the
-// slabs are many rounds per CU, aligned blocks when they are few (28 layers
-// of 4 groups: aligned at one 1920x1080 frame, 30.0 us against 35.6 in pass
-// 1 and 26.2 against 28.1 in pass 2; equal ranges at 30 frames).  At a tie
-// (five frames) pass 2 takes equal ranges, 106 us against 111, and pass 1,
-// whose every segment starts with a reference slab, aligned blocks, 108 us
-// against 113.
+// slab round, the time the block's eight waves take for a slab each.
+//   aligned  whole rounds of the largest block, and a start
+//   equal    pass 1: whole rounds, a start, and for every further segment a
+//            start (its window rows and reference slab, two barriers) and
+//            the rounding of its slabs to whole rounds;
+//            pass 2: the slabs, half a round per segment for that rounding
+//            (a wave goes to the next segment's rows while others finish),
+//            a start, and a quarter round for every further segment.
+// Pass 1's first slab is the reference, which the waves take together as
+// part of the start.  Measured on 28 layers of 4 groups, 7 row blocks, us
+// aligned / equal, at one to eight 1920x1080 frames:
+//   pass 1  31/37 52/56 69/76 88/93 107/112 126/128 143/147 161/162
+//   pass 2  27/30 45/48 65/64 91/84 111/105 134/128 157/148 178/166
+// and pass 1 on 14 layers, one round of 224 blocks / two of 504, at three
+// and five frames: 38/45 62/68.
 // With at most four slabs in a block, several waves share a slab, each with
-// its part of the row blocks.
+// its part of the row blocks (share: where the kernel can).
 inline SlabLaunch slab_grid(int Lp, int nlg, int nrb, int n_cu, int max_per_lg, bool share,
-                            bool equal) {
+                            bool first) {
   SlabLaunch l;
   SlabGrid& g = l.g;
   g.S = (Lp + kSlab - 1) / kSlab;
-  constexpr int kStart = 8;   // a block's start: about one round
+  const int start = first ? 10 : 8;
   auto waves_per_slab = [&](int64_t slabs) {
     int rs = 1;
     while (share && rs * 2 * slabs <= kSlabWaves && rs * 2 <= nrb) rs *= 2;
@@ -101,7 +107,8 @@ inline SlabLaunch slab_grid(int Lp, int nlg, int nrb, int n_cu, int max_per_lg, 
   };
   auto rounds8 = [&](int64_t slabs) {
     const int rs = waves_per_slab(slabs);
-    return rs > 1 ? 8 / rs : (slabs + kSlabWaves - 1) / kSlabWaves * 8;
+    if (rs > 1) return (int64_t)(8 / rs);
+    return (slabs - first + kSlabWaves - 1) / kSlabWaves * 8;
   };
   const int64_t total = (int64_t)g.S * nlg;
   int64_t best = -1;
@@ -109,7 +116,7 @@ inline SlabLaunch slab_grid(int Lp, int nlg, int nrb, int n_cu, int max_per_lg, 
                                            std::max<int64_t>(1, 4L * n_cu / nlg)});
   for (int64_t p = 1; p <= p_max; ++p) {
     const int64_t q = (g.S + p - 1) / p;
-    const int64_t cost = (p * nlg + n_cu - 1) / n_cu * (rounds8(q) + kStart);
+    const int64_t cost = (p * nlg + n_cu - 1) / n_cu * (rounds8(q) + start);
     if (best < 0 || cost <= best) {
       best = cost;
       g.per_lg = (int)p;
@@ -121,10 +128,12 @@ inline SlabLaunch slab_grid(int Lp, int nlg, int nrb, int n_cu, int max_per_lg, 
   }
   if (total > n_cu) {
     const int64_t q = (total + n_cu - 1) / n_cu, q_min = total / n_cu;
-    const int64_t segs = (q + g.S - 2) / g.S + 1;
+    const int64_t segs = (q + g.S - 2) / g.S + 1;           // of a block at most
     const int64_t chunks = (g.S + q_min - 2) / q_min + 1;   // blocks per group at most
-    const int64_t cost = (q + kSlabWaves - 1) / kSlabWaves * 8 + kStart + (segs - 1) * (8 + kStart);
-    if (chunks <= max_per_lg && (equal ? cost <= best : cost < best)) {
+    const int64_t cost = first ? (q + kSlabWaves - 1) / kSlabWaves * 8 + start +
+                                     (segs - 1) * (8 + start)
+                               : q + segs * 4 + start + (segs - 1) * 2;
+    if (chunks <= max_per_lg && cost < best) {
       g.per_lg = 0;
       g.q = (int)q_min;
       g.r = (int)(total - q_min * n_cu);
@@ -150,8 +159,8 @@ inline SlabLaunch slab_grid(int Lp, int nlg, int nrb, int n_cu, int max_per_lg, 
 // pass 2 at 184 blocks 6.1 / 7.9, 368 blocks 8.8 / 9.3, 528 blocks 11.1 / 9.8.
 inline void slab_launches(int Lp, int nlg, int nrb, int n_cu, int max_chunks, bool one_sum,
                           bool whole_blocks, SlabLaunch* p1, SlabLaunch* p2) {
-  *p1 = slab_grid(Lp, nlg, nrb, n_cu, max_chunks, true, false);
-  *p2 = slab_grid(Lp, nlg, nrb, n_cu, 1 << 30, one_sum, true);
+  *p1 = slab_grid(Lp, nlg, nrb, n_cu, max_chunks, true, true);
+  *p2 = slab_grid(Lp, nlg, nrb, n_cu, 1 << 30, one_sum, false);
   if (nrb > kSmallWaves) return;
   const int64_t chunks = (Lp + kSmallRows - 1) / kSmallRows;
   if (chunks <= max_chunks && chunks * nlg <= n_cu) {

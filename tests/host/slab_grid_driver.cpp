@@ -1,7 +1,7 @@
 // Checks the scoring passes' division of slabs into blocks (slab_grid.h, the
 // same source the library compiles) for each "Lp nlg nrb n_cu max_chunks
-// one_sum whole_blocks" line of stdin: prints "ok", or what is wrong, and
-// the two passes' kinds.
+// one_sum whole_blocks" line of stdin: prints "ok", or what is wrong, the
+// two passes' kinds and their block counts.
 #include <cstdio>
 #include <string>
 #include <vector>
@@ -50,9 +50,9 @@ int main() {
     if (!bad && p2.small) bad = p2.blocks == p2.g.S * nlg && whole ? nullptr : "small pass 2";
     else if (!bad) bad = check(p2, nlg, mc, false);
     if (!bad && !one && p2.g.rs != 1) bad = "shared slabs with several outputs";
-    std::printf("%s %s %s\n", bad ? bad : "ok",
+    std::printf("%s %s %s %d %d\n", bad ? bad : "ok",
                 p1.small ? "small" : p1.g.per_lg ? "aligned" : "crossing",
-                p2.small ? "small" : p2.g.per_lg ? "aligned" : "crossing");
+                p2.small ? "small" : p2.g.per_lg ? "aligned" : "crossing", p1.blocks, p2.blocks);
   }
   return 0;
 }

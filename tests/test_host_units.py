@@ -160,3 +160,33 @@ def test_scoring_slab_division(tmp_path):
     assert not bad, bad[:10]
     for p in (1, 2):
         assert {o.split()[p] for o in out} == {"small", "aligned", "crossing"}
+
+
+def _launches(tmp_path, lines):
+    exe = _build(tmp_path, "slab_grid", [os.path.join(HOST, "slab_grid_driver.cpp")],
+                 sanitize=False)
+    r = subprocess.run([exe], input="".join(" ".join(map(str, x)) + "\n" for x in lines),
+                       capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stderr
+    out = [line.split() for line in r.stdout.splitlines()]
+    assert all(o[0] == "ok" for o in out) and len(out) == len(lines)
+    return [(o[1], o[2], int(o[3]), int(o[4])) for o in out]
+
+
+def test_scoring_division_between_frame_counts(tmp_path):
+    """The division of each pass on 256 CUs where both were timed, one to
+    twelve 1920x1080 frames (2,691 visual tokens each, 224 text tokens) on 4
+    groups: aligned blocks where they were the faster, ranges crossing groups
+    where those were, either where they are within 2% of each other."""
+    frames = [1, 2, 3, 4, 5, 6, 7, 8, 10, 12]
+    tok = [f * 2691 + 224 for f in frames]
+    got = _launches(tmp_path, [(t, 28 * 4, 7, 256, -(-t // 256), 1, 1) for t in tok])
+    pass1 = "aligned aligned aligned aligned aligned - - - crossing crossing".split()
+    pass2 = "aligned aligned - crossing crossing crossing crossing crossing crossing crossing".split()
+    for f, a, b, g in zip(frames, pass1, pass2, got):
+        assert a in ("-", g[0]), (f, "pass 1", g)
+        assert b in ("-", g[1]), (f, "pass 2", g)
+    # three and five frames on 14 layers: pass 1 in one round of 4 blocks per
+    # group, whose reference slab is no part of the rounds, not two rounds of 9
+    got = _launches(tmp_path, [(t, 14 * 4, 7, 256, -(-t // 256), 1, 1) for t in (8297, 13679)])
+    assert [g[2] for g in got] == [224, 224], got
