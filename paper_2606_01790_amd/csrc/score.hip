@@ -101,12 +101,11 @@ int launch_score(const Geometry& g, const starkv_params& p, const void* q,
   a.part = reinterpret_cast<float2*>(static_cast<char*>(ws) + wl.part_off);
   a.sraw = reinterpret_cast<float*>(static_cast<char*>(ws) + wl.sraw_off);
   // pass 1 leaves one record per block and group (the workspace holds
-  // n_chunks_max); pass 2 may split finer, and shares slabs only where one
-  // sum per group is wanted
+  // n_chunks_max); pass 2 may split finer
   const int nlg = g.n_layers * g.G;
   SlabLaunch p1, p2;
   slab_launches(g.Lp, nlg, a.nrb, n_cu, a.n_chunks_max, a.n_out == 1,
-                a.n_out == 1 || a.W % 32 == 0, &p1, &p2);
+                a.n_out == 1 || a.W % 32 == 0, g.d, g.esz, &p1, &p2);
 
   const int err = g.dtype == STARKV_BF16 ? run_score_bf16(a, g.d, p1, p2, st)
                                          : run_score_f32(a, g.d, p1, p2, st);

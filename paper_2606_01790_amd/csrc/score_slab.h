@@ -813,8 +813,6 @@ __global__ __launch_bounds__(kSlabThreads) void score_pass2(ScoreArgs a, SlabGri
 // tokens, 42.8 / 46.5 at 5,600, 106 / 112 at 13,679.  At 14 row blocks its
 // registers spill and the rolled one is the faster (1771 / 1792 us at
 // 140,190 tokens).
-constexpr int kUnrolledBlocks = 8;
-
 template <int NRB, bool PH>
 __global__ __launch_bounds__(kSlabThreads) void score_pass2_unrolled(ScoreArgs a, SlabGrid sg,
                                                                      SlabGrid sg1) {
@@ -1157,7 +1155,7 @@ int run_passes(const ScoreArgs& a, const SlabLaunch& p1, const SlabLaunch& p2, h
   if (p2.small)
     score_pass2_small<T, D><<<p2.blocks, kSmallWaves * 64,
                               (size_t)kSlab * Shape<T, D>::kQStride, st>>>(a, p2.g.S, p1.g);
-  else if (kPipe && D == 128 && a.nrb <= kUnrolledBlocks && (a.n_out == 1 || a.W % 32 == 0))
+  else if (pass2_unrolled(D, (int)sizeof(T), a.nrb, a.n_out == 1 || a.W % 32 == 0))
     run_unrolled(a, p2, p1.g, st);
   else if (a.n_out == 1)
     score_pass2<T, D, kGroup, kPipe><<<p2.blocks, kSlabThreads, lds2, st>>>(a, p2.g, p1.g);

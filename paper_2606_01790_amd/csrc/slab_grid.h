@@ -16,6 +16,13 @@ constexpr int kSlab = 64;           // tokens per slab
 constexpr int kSlabWaves = 8;       // waves of a persistent block
 constexpr int kSmallRows = 256;     // tokens of a small-call block in pass 1
 constexpr int kSmallWaves = 8;      // row blocks (a wave each) of a small-call block at most
+constexpr int kUnrolledBlocks = 8;  // row blocks of the unrolled pass 2 at most
+
+// Whether pass 2 runs the unrolled kernel, whose waves take whole slabs
+// (whole_blocks: an output's rows are whole row blocks).
+inline bool pass2_unrolled(int d, int esz, int nrb, bool whole_blocks) {
+  return esz == 2 && d == 128 && nrb <= kUnrolledBlocks && whole_blocks;
+}
 
 STARKV_HD inline int slab_min(int a, int b) { return a < b ? a : b; }
 
@@ -93,7 +100,7 @@ STARKV_HD inline int slab_chunks(const SlabGrid& g, int lg) {
 // and pass 1 on 14 layers, one round of 224 blocks / two of 504, at three
 // and five frames: 38/45 62/68.
 // With at most four slabs in a block, several waves share a slab, each with
-// its part of the row blocks (share: where the kernel can).
+// its part of the row blocks, where the kernel can (share).
 inline SlabLaunch slab_grid(int Lp, int nlg, int nrb, int n_cu, int max_per_lg, bool share,
                             bool first) {
   SlabLaunch l;
@@ -146,8 +153,8 @@ inline SlabLaunch slab_grid(int Lp, int nlg, int nrb, int n_cu, int max_per_lg, 
 
 // The two passes' launches for n_layers * G groups of nrb row blocks, at most
 // max_chunks records per group in the workspace.  one_sum: one output per
-// group (waves may then share a slab in pass 2); whole_blocks: an output's
-// rows are whole row blocks.
+// group (waves may then share a slab in pass 2, but not in its unrolled
+// kernel); whole_blocks: an output's rows are whole row blocks.
 //
 // The small-call kernels run one short step per block and win while the
 // blocks run side by side: pass 1 (a block per CU fits beside another, but
@@ -158,9 +165,11 @@ inline SlabLaunch slab_grid(int Lp, int nlg, int nrb, int n_cu, int max_per_lg, 
 // blocks 8.0 / 11.0, 240 and 264 blocks 13.5 / 11.5, 288 blocks 13.0 / 11.2;
 // pass 2 at 184 blocks 6.1 / 7.9, 368 blocks 8.8 / 9.3, 528 blocks 11.1 / 9.8.
 inline void slab_launches(int Lp, int nlg, int nrb, int n_cu, int max_chunks, bool one_sum,
-                          bool whole_blocks, SlabLaunch* p1, SlabLaunch* p2) {
+                          bool whole_blocks, int d, int esz, SlabLaunch* p1,
+                          SlabLaunch* p2) {
+  const bool unrolled = pass2_unrolled(d, esz, nrb, whole_blocks);
   *p1 = slab_grid(Lp, nlg, nrb, n_cu, max_chunks, true, true);
-  *p2 = slab_grid(Lp, nlg, nrb, n_cu, 1 << 30, one_sum, false);
+  *p2 = slab_grid(Lp, nlg, nrb, n_cu, 1 << 30, one_sum && !unrolled, false);
   if (nrb > kSmallWaves) return;
   const int64_t chunks = (Lp + kSmallRows - 1) / kSmallRows;
   if (chunks <= max_chunks && chunks * nlg <= n_cu) {

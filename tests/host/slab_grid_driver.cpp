@@ -1,6 +1,6 @@
 // Checks the scoring passes' division of slabs into blocks (slab_grid.h, the
 // same source the library compiles) for each "Lp nlg nrb n_cu max_chunks
-// one_sum whole_blocks" line of stdin: prints "ok", or what is wrong, the
+// one_sum whole_blocks [d element-bytes]" line of stdin: prints "ok", or what is wrong, the
 // two passes' kinds and their block counts.
 #include <cstdio>
 #include <string>
@@ -35,10 +35,14 @@ static const char* check(const SlabLaunch& l, int nlg, int max_chunks, bool reco
 }
 
 int main() {
-  int Lp, nlg, nrb, n_cu, mc, one, whole;
-  while (std::scanf("%d %d %d %d %d %d %d", &Lp, &nlg, &nrb, &n_cu, &mc, &one, &whole) == 7) {
+  char line[256];
+  while (std::fgets(line, sizeof line, stdin)) {
+    int Lp, nlg, nrb, n_cu, mc, one, whole, d = 64, esz = 2;
+    if (std::sscanf(line, "%d %d %d %d %d %d %d %d %d", &Lp, &nlg, &nrb, &n_cu, &mc, &one,
+                    &whole, &d, &esz) < 7)
+      return 1;
     SlabLaunch p1, p2;
-    slab_launches(Lp, nlg, nrb, n_cu, mc, one != 0, whole != 0, &p1, &p2);
+    slab_launches(Lp, nlg, nrb, n_cu, mc, one != 0, whole != 0, d, esz, &p1, &p2);
     const char* bad = nullptr;
     if (p1.small) {   // its blocks take kSmallRows tokens each
       const int n = (Lp + kSmallRows - 1) / kSmallRows;
@@ -50,6 +54,8 @@ int main() {
     if (!bad && p2.small) bad = p2.blocks == p2.g.S * nlg && whole ? nullptr : "small pass 2";
     else if (!bad) bad = check(p2, nlg, mc, false);
     if (!bad && !one && p2.g.rs != 1) bad = "shared slabs with several outputs";
+    if (!bad && pass2_unrolled(d, esz, nrb, whole != 0) && p2.g.rs != 1)
+      bad = "shared slabs in the unrolled kernel";
     std::printf("%s %s %s %d %d\n", bad ? bad : "ok",
                 p1.small ? "small" : p1.g.per_lg ? "aligned" : "crossing",
                 p2.small ? "small" : p2.g.per_lg ? "aligned" : "crossing", p1.blocks, p2.blocks);

@@ -180,7 +180,7 @@ def test_scoring_division_between_frame_counts(tmp_path):
     where those were, either where they are within 2% of each other."""
     frames = [1, 2, 3, 4, 5, 6, 7, 8, 10, 12]
     tok = [f * 2691 + 224 for f in frames]
-    got = _launches(tmp_path, [(t, 28 * 4, 7, 256, -(-t // 256), 1, 1) for t in tok])
+    got = _launches(tmp_path, [(t, 28 * 4, 7, 256, -(-t // 256), 1, 1, 128, 2) for t in tok])
     pass1 = "aligned aligned aligned aligned aligned - - - crossing crossing".split()
     pass2 = "aligned aligned - crossing crossing crossing crossing crossing crossing crossing".split()
     for f, a, b, g in zip(frames, pass1, pass2, got):
@@ -188,5 +188,14 @@ def test_scoring_division_between_frame_counts(tmp_path):
         assert b in ("-", g[1]), (f, "pass 2", g)
     # three and five frames on 14 layers: pass 1 in one round of 4 blocks per
     # group, whose reference slab is no part of the rounds, not two rounds of 9
-    got = _launches(tmp_path, [(t, 14 * 4, 7, 256, -(-t // 256), 1, 1) for t in (8297, 13679)])
+    got = _launches(tmp_path, [(t, 14 * 4, 7, 256, -(-t // 256), 1, 1, 128, 2) for t in (8297, 13679)])
     assert [g[2] for g in got] == [224, 224], got
+
+
+def test_unrolled_pass_shares_no_slab(tmp_path):
+    """The unrolled pass-2 kernel gives each wave whole slabs, so its division
+    is estimated without waves sharing one; the rolled kernel's may share."""
+    lines = [(Lp, nlg, nrb, n_cu, -(-Lp // 256), 1, 1, 128, 2)
+             for Lp in (64, 700, 2915, 5606, 13679) for nlg in (2, 8, 16, 56, 112)
+             for nrb in (1, 4, 7, 8) for n_cu in (256, 304)]
+    _launches(tmp_path, lines)
