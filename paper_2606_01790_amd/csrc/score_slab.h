@@ -1129,15 +1129,27 @@ __global__ __launch_bounds__(kSmallWaves * 64) void score_pass2_small(ScoreArgs 
   a.sraw[((size_t)lg * a.n_out + wave) * a.Lp + t0 + lane] = v;
 }
 
-inline void run_unrolled(const ScoreArgs& a, const SlabLaunch& p2, const SlabGrid& g1,
-                         hipStream_t st) {
-  switch (a.nrb) {
+// Pass 2 with one sum per group, or heads of whole row blocks.  The unrolled
+// kernels are compiled only for the keys they serve.
+template <typename T, int D>
+void run_pass2_blocks(const ScoreArgs& a, const SlabLaunch& p2, const SlabGrid& g1,
+                      hipStream_t st) {
+  constexpr bool kPipe = sizeof(T) == 2;   // tiles interleaved
+  if constexpr (pass2_unrolled(D, (int)sizeof(T), 1, true)) {
+    switch (a.nrb) {
 #define STARKV_NRB(n) \
-  case n: launch_unrolled<n>(a, p2, g1, st); break;
-    STARKV_NRB(1) STARKV_NRB(2) STARKV_NRB(3) STARKV_NRB(4) STARKV_NRB(5) STARKV_NRB(6)
-    STARKV_NRB(7) STARKV_NRB(8)
+  case n: return launch_unrolled<n>(a, p2, g1, st);
+      STARKV_NRB(1) STARKV_NRB(2) STARKV_NRB(3) STARKV_NRB(4) STARKV_NRB(5) STARKV_NRB(6)
+      STARKV_NRB(7) STARKV_NRB(8)
 #undef STARKV_NRB
+    }
+    static_assert(kUnrolledBlocks == 8, "a case for every unrolled row-block count");
   }
+  const size_t lds = pass2_lds<T, D>(a.nrb);
+  if (a.n_out == 1)
+    score_pass2<T, D, kGroup, kPipe><<<p2.blocks, kSlabThreads, lds, st>>>(a, p2.g, g1);
+  else
+    score_pass2<T, D, kHeadBlocks, kPipe><<<p2.blocks, kSlabThreads, lds, st>>>(a, p2.g, g1);
 }
 
 template <typename T, int D>
@@ -1155,14 +1167,10 @@ int run_passes(const ScoreArgs& a, const SlabLaunch& p1, const SlabLaunch& p2, h
   if (p2.small)
     score_pass2_small<T, D><<<p2.blocks, kSmallWaves * 64,
                               (size_t)kSlab * Shape<T, D>::kQStride, st>>>(a, p2.g.S, p1.g);
-  else if (pass2_unrolled(D, (int)sizeof(T), a.nrb, a.n_out == 1 || a.W % 32 == 0))
-    run_unrolled(a, p2, p1.g, st);
-  else if (a.n_out == 1)
-    score_pass2<T, D, kGroup, kPipe><<<p2.blocks, kSlabThreads, lds2, st>>>(a, p2.g, p1.g);
-  else if (a.W % 32 == 0)
-    score_pass2<T, D, kHeadBlocks, kPipe><<<p2.blocks, kSlabThreads, lds2, st>>>(a, p2.g, p1.g);
-  else
+  else if (a.n_out > 1 && a.W % 32 != 0)
     score_pass2<T, D, kHeadGroups, false><<<p2.blocks, kSlabThreads, lds2, st>>>(a, p2.g, p1.g);
+  else
+    run_pass2_blocks<T, D>(a, p2, p1.g, st);
   return (int)hipGetLastError();
 }
 

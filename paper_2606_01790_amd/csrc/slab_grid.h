@@ -20,7 +20,7 @@ constexpr int kUnrolledBlocks = 8;  // row blocks of the unrolled pass 2 at most
 
 // Whether pass 2 runs the unrolled kernel, whose waves take whole slabs
 // (whole_blocks: an output's rows are whole row blocks).
-inline bool pass2_unrolled(int d, int esz, int nrb, bool whole_blocks) {
+constexpr bool pass2_unrolled(int d, int esz, int nrb, bool whole_blocks) {
   return esz == 2 && d == 128 && nrb <= kUnrolledBlocks && whole_blocks;
 }
 

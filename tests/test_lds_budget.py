@@ -109,3 +109,16 @@ def test_select_kernel_lds_fits(tmp_path):
     dynamic = 4 * _const(src, "kSelLdsKeys")
     static = _static_lds(path, "select_kernel", tmp_path)
     assert static + dynamic <= LDS_LIMIT, (static, dynamic)
+
+
+@needs_hipcc
+def test_float32_unit_holds_float32_kernels_only(tmp_path):
+    """The unrolled pass 2 serves bf16 keys with d = 128 alone; the float32
+    unit, which can never choose it, does not compile its sixteen kernels."""
+    path = os.path.join(B.CSRC, "score_f32.hip")
+    out = tmp_path / "score_f32.s"
+    flags = [f for f in B.HIP_FLAGS if f != "-fPIC"]
+    subprocess.run([B.HIPCC, *flags, "-I", B.INCLUDE, "--cuda-device-only", "-S",
+                    "-o", str(out), path], check=True, capture_output=True)
+    names = re.findall(r"\.name:\s+(\S*score_pass\S*)", out.read_text())
+    assert names and not [n for n in names if "unrolled" in n or "DF16b" in n], names
