@@ -590,6 +590,17 @@ __global__ __launch_bounds__(kSlabThreads) void score_pass1(ScoreArgs a, SlabGri
 // 2^(y - c) vanishes in pass 2.  The first records are loaded ahead by
 // merge_issue.
 constexpr int kMergeBatch = 8;
+// M + log2(l).  The logarithm is off by up to an ulp of its result, to one
+// side: taken of l, about 2^10 in ordinary calls and up to 2^32 under high
+// logits, that was most of S's error.  Of l's mantissa in [0.5, 1) it is off
+// by 2^-24 at most, and the sum is rounded once.  28 layers of 4 groups,
+// 2,915 tokens, S against 64 bits: 3.1e-7 and 6.3e-8; with a key 24 log2
+// units above the others in every group 3.6e-7 and 6.2e-8.
+__device__ __forceinline__ float add_log2(float M, float l) {
+  int e;
+  const float m = frexpf(l, &e);
+  return (float)((double)M + ((double)e + (double)log2f(m)));
+}
 __device__ __forceinline__ void merge_issue(const ScoreArgs& a, const float2* part, int n_chunks,
                                             int c0, int r, float2 (&p)[kMergeBatch]) {
 #pragma unroll
@@ -613,7 +624,7 @@ __device__ __forceinline__ float merge_row(const ScoreArgs& a, const float2* par
     if ((c0 += kMergeBatch) >= n_chunks) break;
     merge_issue(a, part, n_chunks, c0, r, p);
   }
-  return (r < a.R) ? Mx + log2f(lx) : INFINITY;
+  return (r < a.R) ? add_log2(Mx, lx) : INFINITY;
 }
 
 // ---------------------------------------------------------------- pass 2

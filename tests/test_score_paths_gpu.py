@@ -83,3 +83,54 @@ def test_sums_beyond_the_reference(form):
     """Logits that rise by more than 64 log2 units inside a block: its row
     sums are redone against running maxima."""
     _run(*form, spike=24.0)
+
+
+def _layers_error(nl, H, G, d, W, Lp, dtype, top, layers, fill=None):
+    """S against 64 bits over some layers, unpooled: the 2-norm of the
+    difference over that of the result.  Every group has one key (at a third
+    of the cache) about `top` log2 units above the others, if any; fill =
+    (rows, level): the last keys, at about `level`."""
+    import torch
+    from paper_2606_01790_amd import starkv as sk
+    g = torch.Generator(device="cuda").manual_seed(Lp)
+    tt = torch.float32 if dtype == "f32" else torch.bfloat16
+    L = Lp + W
+    k = torch.empty(nl, G, L, d, dtype=tt, device="cuda").normal_(generator=g)
+    u = torch.randint(0, 2, (nl, G, d), generator=g, device="cuda").float() * 2 - 1
+    q = torch.randn(nl, H, W, d, generator=g, device="cuda")
+    q = (q + (3 * u.repeat_interleave(H // G, 1)[:, :, None] if top or fill else 0)).to(tt)
+    unit = 3 * math.sqrt(d) * math.log2(math.e)      # q.u of a key u, in log2 units
+    if top:
+        k[:, :, Lp // 3] = (top / unit * u).to(tt)
+    if fill:
+        k[:, :, Lp - fill[0]:Lp] = (fill[1] / unit * u).to(tt)[:, :, None]
+    dims = sk.make_dims(nl, H, G, d, L, W, sk.F32 if dtype == "f32" else sk.BF16, False)
+    p = sk.params_default()
+    p.pool_kernel = 1
+    S = torch.empty(nl, G, Lp, device="cuda")
+    sbar = torch.empty(nl, Lp, device="cuda")
+    gstar = torch.empty(nl, Lp, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(sk.workspace_bytes(dims), dtype=torch.uint8, device="cuda")
+    sk.score(dims, p, q, k, sk.contiguous_layout(k, dims), S, sbar, gstar, ws)
+    num = den = 0.0
+    for l in layers:
+        for i in range(G):
+            kk = k[l, i, :Lp].double().t().contiguous()
+            y = q[l, i * (H // G):(i + 1) * (H // G)].double().reshape(-1, d) @ kk
+            ref = torch.softmax(y / math.sqrt(d), 1).sum(0) / (H // G)
+            num += float((S[l, i].double() - ref).pow(2).sum())
+            den += float(ref.pow(2).sum())
+    return math.sqrt(num / den)
+
+
+@pytest.mark.parametrize("form,top", [((28, 28, 4, 128, 32, 2915, "bf16"), 0),
+                                      ((28, 28, 4, 128, 32, 2915, "bf16"), 24),
+                                      ((28, 14, 2, 64, 32, 9001, "bf16"), 0),
+                                      ((16, 16, 4, 128, 8, 4114, "f32"), 0)])
+def test_row_sums_logarithm_is_unbiased(form, top):
+    """S over many rows: each row's own roundings (of y, c and y - c, half an
+    ulp each) average out over a group's 32 to 224 rows.  What is left: the
+    exponential's error, at most an ulp (2^-23), which may lean to one side,
+    and the sums', as much again.  A logarithm of the whole row sum adds up to
+    an ulp of about 10 (2^-20), or of 24, to one side (3.1e-7, 3.6e-7)."""
+    assert _layers_error(*form, top, range(2)) <= 2.0 ** -22
