@@ -70,10 +70,11 @@ namespace {
 constexpr int kSlabThreads = kSlabWaves * 64;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegBig = -1e30f;
-// A block's sum against its reference stays below this unless a logit rises
-// about 64 log2 units above the reference slab; then the block's row
-// statistics are redone against exact running maxima.
-constexpr float kSumLimit = 18446744073709551616.0f;   // 2^64
+// A row's sum over a block against its reference stays below this unless a
+// logit rises about 32 log2 units above the reference slab.  An exponent's
+// rounding grows with its size (up to 2^-20 below 32), so such a block's
+// sums are taken again, against a higher reference (sum_again).
+constexpr float kSumLimit = 4294967296.0f;   // 2^32
 
 // Pass-2 output: one sum per group; one per head, a head being whole row
 // blocks; one per head, a head being whole 8-row groups.
@@ -381,9 +382,62 @@ __host__ __device__ constexpr size_t pass1_lds(int nrb) {
          (sums > slab ? sums : slab);
 }
 
+// Row r's sum over the block: every wave's part, both lane halves.
+__device__ __forceinline__ float row_sum(const ScoreArgs& a, const float* l_s, int r) {
+  float l = 0.f;
+  const float* lr = l_s + (r >> 5) * 64 + (r & 31);
+#pragma unroll
+  for (int v = 0; v < kSlabWaves; ++v) l += lr[v * a.nrb * 64] + lr[v * a.nrb * 64 + 32];
+  return l;
+}
+
+// The sums of slabs [s0, s1) again where a row's (out) left its range: that
+// row's reference rises to M_r + log2(sum), within log2 of the token count of
+// its maximum.  True if a sum is not finite.  Apart from the first sums' loop, whose schedule suffers
+// from a second use; it takes whole slabs per wave without loading ahead.
+// Every group with a key 98 log2 units above the others, 28 layers of 4
+// groups, whole score call: 77 us at 2,915 tokens and 303 at 13,679; with
+// exact_rows instead 128 and 528; without such keys 60 and 212.
+template <typename T, int D>
+__device__ bool sum_again(const ScoreArgs& a, const T* kg, const char* qs, float* ms_s, float* l_s,
+                          int s0, int s1, float2* out) {
+  using SH = Shape<T, D>;
+  const int tid = tid_here(), lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
+  bool bad = false;
+  for (int r = tid; r < a.nrb * 32; r += kSlabThreads) {
+    const float l = out[r].y;   // this thread's own store
+    bad |= !(l < INFINITY);
+    if (l >= kSumLimit) ms_s[r] += log2f(l);
+  }
+  float* lw = l_s + wave * a.nrb * 64 + lane;
+  for (int rb = 0; rb < a.nrb; ++rb) lw[rb * 64] = 0.f;
+  __syncthreads();
+  for (int slab = s0 + wave; slab < s1; slab += kSlabWaves) {
+    for (int cb = 0; cb < 2; cb += SH::kTB) {
+      KFrags<T, D> kf;
+      load_k<T, D>(a, kg, slab, cb, kf);
+      for (int rb = 0; rb < a.nrb; ++rb) {
+        i32x4 qf[SH::kNP];
+        load_q<T, D>(qs + (rb * 32 + l32) * SH::kQStride + half * 16, qf);
+        float s = 0.f;
+#pragma unroll
+        for (int u = 0; u < SH::kTB; ++u) {
+          f32x16 acc = chain<T, D, true>(qf, kf[u]);
+          if (slab == s1 - 1) mask_tokens(acc, slab * kSlab + (cb + u) * 32, a.Lp);
+          s += tile_sum1(acc, a.scale, ms_s[rb * 32 + l32]);
+        }
+        lw[rb * 64] += s;
+      }
+    }
+  }
+  __syncthreads();
+  for (int r = tid; r < a.nrb * 32; r += kSlabThreads)
+    out[r] = make_float2(ms_s[r], row_sum(a, l_s, r));
+  return bad;
+}
+
 // Exact row statistics of slabs [s0, s1) against running maxima, for blocks
-// whose sums left the range of their references (or are not numbers): a
-// wave per row block, K re-read for each.
+// with sums that are not finite: a wave per row block, K re-read for each.
 template <typename T, int D>
 __device__ void exact_rows(const ScoreArgs& a, const T* kg, const char* qs, int s0, int s1,
                            float2* out) {
@@ -569,16 +623,19 @@ __global__ __launch_bounds__(kSlabThreads) void score_pass1(ScoreArgs a, SlabGri
     float2* out = a.part + ((size_t)w.lg * a.n_chunks_max + w.chunk) * (a.nrb * 32);
     bool bad = false;
     for (int r = tid_here(); r < a.nrb * 32; r += kSlabThreads) {
-      float l = 0.f;
-      const float* lr = l_s + (r >> 5) * 64 + (r & 31);
-#pragma unroll
-      for (int v = 0; v < kSlabWaves; ++v) l += lr[v * a.nrb * 64] + lr[v * a.nrb * 64 + 32];
+      const float l = row_sum(a, l_s, r);
       out[r] = make_float2(ms_s[r], l);
       bad |= !(l < kSumLimit);
     }
     if (bad) *redo = 1;
     __syncthreads();
-    if (*redo) exact_rows<T, D>(a, kg, qs, w.s0, w.s1, out);
+    if (*redo) {
+      __syncthreads();   // the flag is read
+      if (threadIdx.x == 0) *redo = 0;
+      if (sum_again<T, D>(a, kg, qs, ms_s, l_s, w.s0, w.s1, out)) *redo = 1;
+      __syncthreads();
+      if (*redo) exact_rows<T, D>(a, kg, qs, w.s0, w.s1, out);
+    }
     if (w.left <= 0) break;
     __syncthreads();   // the next segment overwrites the LDS
   }

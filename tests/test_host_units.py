@@ -199,3 +199,21 @@ def test_unrolled_pass_shares_no_slab(tmp_path):
              for Lp in (64, 700, 2915, 5606, 13679) for nlg in (2, 8, 16, 56, 112)
              for nrb in (1, 4, 7, 8) for n_cu in (256, 304)]
     _launches(tmp_path, lines)
+
+
+def _form_launches(tmp_path, forms):
+    """The launches on 256 CUs of (layers, H, G, d, W, Lp, dtype, per_head)
+    scoring calls."""
+    lines = []
+    for nl, H, G, d, W, Lp, dtype, per_head in forms:
+        one = not per_head or H == G
+        lines.append((Lp, nl * G, -(-W * (H // G) // 32), 256, -(-Lp // 256), int(one),
+                      int(one or W % 32 == 0), d, 4 if dtype == "f32" else 2))
+    return [g[:2] for g in _launches(tmp_path, lines)]
+
+
+def test_score_forms_cross_groups(tmp_path):
+    """The shapes that the GPU tests of crossing blocks use give crossing
+    blocks in both passes."""
+    from tests.test_score_paths_gpu import CROSSING
+    assert set(_form_launches(tmp_path, CROSSING)) == {("crossing", "crossing")}

@@ -11,7 +11,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-def _run(nl, H, G, d, W, Lp, dtype, per_head, spike):
+def _run(nl, H, G, d, W, Lp, dtype, per_head, spike, at=None):
     import torch
     from paper_2606_01790_amd import starkv as sk
     g = torch.Generator(device="cuda").manual_seed(nl * 1000 + Lp)
@@ -20,9 +20,9 @@ def _run(nl, H, G, d, W, Lp, dtype, per_head, spike):
     k = torch.randn(nl, G, L + 3, d, generator=g, device="cuda").to(tt)
     q = torch.randn(nl, H, W, d, generator=g, device="cuda").to(tt)
     if spike:
-        # keys that grow along the cache and one far above the rest, neither
-        # in a block's last slab
-        k[:, :, Lp // 3] *= spike
+        # keys that grow along the cache and one far above the rest (at a
+        # third of it, or `at`), neither in a block's last slab
+        k[:, :, Lp // 3 if at is None else at] *= spike
         k[:, :, :Lp // 2] *= torch.linspace(0.1, 4.0, Lp // 2, device="cuda").to(tt)[:, None]
     dims = sk.make_dims(nl, H, G, d, L, W, sk.F32 if dtype == "f32" else sk.BF16, per_head)
     p = sk.params_default()
@@ -89,7 +89,7 @@ def _layers_error(nl, H, G, d, W, Lp, dtype, top, layers, fill=None):
     """S against 64 bits over some layers, unpooled: the 2-norm of the
     difference over that of the result.  Every group has one key (at a third
     of the cache) about `top` log2 units above the others, if any; fill =
-    (rows, level): the last keys, at about `level`."""
+    (rows, level): the last keys, at about `level`, and the others low."""
     import torch
     from paper_2606_01790_amd import starkv as sk
     g = torch.Generator(device="cuda").manual_seed(Lp)
@@ -100,6 +100,8 @@ def _layers_error(nl, H, G, d, W, Lp, dtype, top, layers, fill=None):
     q = torch.randn(nl, H, W, d, generator=g, device="cuda")
     q = (q + (3 * u.repeat_interleave(H // G, 1)[:, :, None] if top or fill else 0)).to(tt)
     unit = 3 * math.sqrt(d) * math.log2(math.e)      # q.u of a key u, in log2 units
+    if fill:
+        k *= 0.1
     if top:
         k[:, :, Lp // 3] = (top / unit * u).to(tt)
     if fill:
@@ -134,3 +136,41 @@ def test_row_sums_logarithm_is_unbiased(form, top):
     and the sums', as much again.  A logarithm of the whole row sum adds up to
     an ulp of about 10 (2^-20), or of 24, to one side (3.1e-7, 3.6e-7)."""
     assert _layers_error(*form, top, range(2)) <= 2.0 ** -22
+
+
+@pytest.mark.parametrize("form", [(28, 28, 28, 128, 1, 2915, "bf16"), (64, 8, 8, 64, 1, 9001, "bf16"),
+                                  (64, 8, 8, 64, 1, 2915, "f32")])
+def test_sums_far_above_their_reference(form):
+    """One window row per group, whose top key (12 log2 units, most of the
+    mass) stands 48 above every block's last slab: the row's statistics are as
+    exact as with a near reference.  Roundings of the row, half an ulp each
+    times ln 2: c below 16, 3.3e-7; against a near reference the exponent of
+    pass 1 below 16, as much, and that of pass 2, near 0; uniform, so a
+    2-norm over the groups of 0.58 of their root sum of squares, 2.7e-7, and
+    2^-22 for the exponential and the sums as above.  Against the last slab an
+    exponent of 32 to 64 is off by up to 1.3e-6, 7.6e-7 in the 2-norm."""
+    nl, H, G, d, W, Lp, dtype = form
+    fill = (Lp - Lp // 3 - 1, -36)      # every key behind the top one
+    err = _layers_error(*form, 12, range(4), fill)
+    assert err <= 2.7e-7 + 2.0 ** -22, err
+
+
+# 130 groups of 63 slabs on 256 CUs: both passes' blocks take equal ranges of
+# 31 or 32 slabs that cross from one group into the next
+CROSSING = [
+    (13, 20, 10, 128, 48, 4001, "bf16", False),
+    (13, 20, 10, 128, 32, 4001, "bf16", True),
+    (13, 20, 10, 64, 32, 4001, "bf16", False),
+    (13, 10, 10, 64, 24, 4001, "f32", False),
+    (13, 20, 10, 128, 32, 4001, "f32", True),
+]
+
+
+@pytest.mark.parametrize("at", [None, -130])
+@pytest.mark.parametrize("form", CROSSING, ids=["-".join(map(str, f)) for f in CROSSING])
+def test_crossing_blocks(form, at):
+    """Blocks of several groups: window rows, references, sums and records of
+    one segment after another.  With a key far above the others 130 tokens
+    before the cache's end, the sums are redone in segments that other
+    segments of the same block follow."""
+    _run(*form, spike=24.0 if at else 0.0, at=at and form[5] + at)
