@@ -138,6 +138,8 @@ constexpr size_t stats_lds() {
   using C = StatsShape<NT>;
   return (size_t)C::kHistInts * 4 + (size_t)C::kKeyCache * 4 + (size_t)C::kCand * 4;
 }
+static_assert(kEntropyBlocks <= (int)(sizeof(StateHeader::ent) / sizeof(double)),
+              "an entropy sum per block in the state header");
 static_assert(StatsShape<1024>::kMaxTies * kTieChunks <= StatsShape<1024>::kKeyCache,
               "tie-split counts live in the key cache");
 static_assert(StatsShape<512>::kMaxTies * kTieChunks <= StatsShape<512>::kKeyCache,
@@ -1269,7 +1271,8 @@ __global__ __launch_bounds__(256) void state_init_kernel(char* state, size_t str
 
 StatsArgs make_stats_args(const Geometry& g, const starkv_params& p, const float* S,
                           const float* sbar, const starkv_span* spans, int32_t n_spans,
-                          int32_t frame, void* state, int32_t frame_cap, float* scalars) {
+                          int32_t frame, void* state, int32_t frame_cap, float* scalars,
+                          int n_cu) {
   StatsArgs a;
   a.S = S;
   a.sbar = sbar;
@@ -1286,7 +1289,7 @@ StatsArgs make_stats_args(const Geometry& g, const starkv_params& p, const float
   a.frame_cap = frame_cap;
   a.sc = (int)scalars_count(g.Ns);
   a.n_stab = stats_stab_blocks(g.Ns);
-  a.n_ent = stats_entropy_blocks(g.Lp, p.aeb_mode == STARKV_AEB_ENTROPY);
+  a.n_ent = stats_entropy_blocks(g.Lp, p.aeb_mode == STARKV_AEB_ENTROPY, g.n_layers, g.Ns, n_cu);
   a.n_layers = g.n_layers;
   a.aeb = p.aeb_mode;
   a.rho_t = p.rho_t;
@@ -1361,14 +1364,18 @@ int launch_stats(const StatsArgs& a, const SelArgs& sel, hipStream_t st) {
   return (int)hipGetLastError();
 }
 
-// The statistics block shape for this call (stats_shape.h); -1 when the
-// device cannot be queried.
-int stats_shape(const Geometry& g, const starkv_params& p) {
+// The current device's CUs; -1 when it cannot be queried.
+int cu_count() {
   int dev = 0, n_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       n_cu <= 0)
     return -1;
+  return n_cu;
+}
+
+// The statistics block shape for this call (stats_shape.h).
+int stats_shape(const Geometry& g, const starkv_params& p, int n_cu) {
   return stats_shape_for((long)stats_layer_blocks(g.Ns) * g.n_layers, n_cu, p.n_bins, p.grid);
 }
 
@@ -1380,10 +1387,11 @@ int launch_update_state(const Geometry& g, const starkv_params& p,
                         int32_t frame, void* state, int32_t frame_cap,
                         float* scalars, void* stream) {
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  const int n_cu = cu_count();
+  if (n_cu < 0) return (int)hipErrorInvalidDevice;
   const StatsArgs a = make_stats_args(g, p, S, sbar, spans, n_spans, frame, state, frame_cap,
-                                      scalars);
-  const int nt = stats_shape(g, p);
-  if (nt < 0) return (int)hipErrorInvalidDevice;
+                                      scalars, n_cu);
+  const int nt = stats_shape(g, p, n_cu);
   SelArgs none{};
   if (nt == 256) return launch_stats<256, false>(a, none, st);
   if (nt == 512) return launch_stats<512, false>(a, none, st);
@@ -1396,9 +1404,9 @@ int launch_update_state_select(const Geometry& g, const starkv_params& p, const 
                                void* state, int32_t frame_cap, float* scalars, int32_t B,
                                float* s, int32_t* idx, void* stream) {
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  const int nt = stats_shape(g, p);
-  if (nt < 0) return (int)hipErrorInvalidDevice;
-  if (nt != 1024) {
+  const int n_cu = cu_count();
+  if (n_cu < 0) return (int)hipErrorInvalidDevice;
+  if (stats_shape(g, p, n_cu) != 1024) {
     // the selection needs a 1024-thread block: two launches
     if (int err = launch_update_state(g, p, S, sbar, spans, n_spans, frame, state, frame_cap,
                                       scalars, stream))
@@ -1406,7 +1414,7 @@ int launch_update_state_select(const Geometry& g, const starkv_params& p, const 
     return launch_select(g, p, sbar, gstar, scalars, spans, n_spans, frame, B, s, idx, stream);
   }
   const StatsArgs a = make_stats_args(g, p, S, sbar, spans, n_spans, frame, state, frame_cap,
-                                      scalars);
+                                      scalars, n_cu);
   SelArgs sel;
   const long room = (long)((stats_lds<1024>() - kSelKeysOff) / sizeof(uint32_t));
   fill_sel_args(sel, g, p, sbar, gstar, scalars, spans, n_spans, frame, B, s, idx,

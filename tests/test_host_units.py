@@ -136,6 +136,27 @@ def test_statistics_block_shape(tmp_path):
     assert got[1][1] == 6 and got[7][1] == 33
 
 
+def test_entropy_blocks(tmp_path):
+    """Four entropy blocks per layer only where they were timed to be faster:
+    long contexts, and launches of at most five blocks per four CUs."""
+    exe = _build(tmp_path, "stats_shape", [os.path.join(HOST, "stats_shape_driver.cpp")],
+                 sanitize=False)
+    cases = [   # (Lp, entropy, layers, subspaces, CUs) -> blocks
+        ((140254, 1, 1, 4, 256), 4), ((140254, 1, 28, 4, 256), 4),
+        ((140254, 1, 35, 4, 256), 4),      # 315 blocks
+        ((140254, 1, 36, 4, 256), 1),      # 324
+        ((140254, 1, 23, 8, 256), 4), ((140254, 1, 25, 8, 256), 1),
+        ((140254, 0, 28, 4, 256), 1),      # the confidence statistic
+        ((98304, 1, 28, 4, 256), 4), ((98303, 1, 28, 4, 256), 1),
+        ((35495, 1, 28, 4, 256), 1), ((35495, 1, 25, 8, 256), 1), ((1, 1, 1, 1, 1), 1),
+    ]
+    r = subprocess.run([exe, "entropy"], capture_output=True, text=True, timeout=60,
+                       input="".join(" ".join(map(str, c)) + "\n" for c, _ in cases))
+    assert r.returncode == 0, r.stderr
+    got = [int(x) for x in r.stdout.split()]
+    assert got == [want for _, want in cases], list(zip(cases, got))
+
+
 def test_scoring_slab_division(tmp_path):
     """Every slab of every (layer, group) belongs to exactly one block of each
     pass, a group's records of pass 1 are numbered from 0 in block order and

@@ -323,7 +323,7 @@ def test_sixty_four_spans(mixed):
 # (frames, rows, cols, gap, per_head, n_bins, grid): the fused binning pass's
 # forms: few keys (one histogram) and many (copies), spans of one shape (cell
 # table) or not, adjacent spans (no cursor) or gaps, cached and uncached keys,
-# every block shape, and the entropy sum split over blocks
+# and every block shape
 FUSED_FORMS = [
     (1, 39, 69, 0, False, 8, 8), (2, 46, 46, 0, False, 8, 8), (5, 39, 69, 0, False, 8, 8),
     (5, 39, 69, 3, False, 8, 8), (12, 51, 91, 0, False, 8, 8), (12, 51, 91, 5, False, 8, 8),
@@ -395,4 +395,12 @@ CACHE_EDGES = [
 def test_key_cache_edges(form):
     """The kernel that keeps the keys in LDS and the one that reads them from
     S, on both sides of every shape's limit."""
+    test_fused_binning_forms(form)
+
+
+@pytest.mark.parametrize("form", [(21, 51, 91, 4, False, 8, 8), (22, 51, 91, 0, False, 8, 8)],
+                         ids=["one-block", "four-blocks"])
+def test_entropy_split(form):
+    """The entropy sum in one block, and from 96K tokens on in four that the
+    layer's finalize adds up."""
     test_fused_binning_forms(form)
