@@ -483,8 +483,6 @@ __global__ __launch_bounds__(kSlabThreads) void score_pass1(ScoreArgs a, SlabGri
   float* l_s = ms_s + a.nrb * 32 + 4;
   const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int units = kSlabWaves / sg.rs, unit = wave / sg.rs, sub = wave % sg.rs;
-  const int rb0 = a.nrb * sub / sg.rs, rb1 = a.nrb * (sub + 1) / sg.rs;
   const char* qlane = qs + l32 * SH::kQStride + half * 16;
   const float* mslane = ms_s + l32;
   float* lw = l_s + wave * a.nrb * 64 + lane;
@@ -495,8 +493,8 @@ __global__ __launch_bounds__(kSlabThreads) void score_pass1(ScoreArgs a, SlabGri
     // the segment's last slab gives the references (below); the waves then
     // take the others, all of them whole
     const int end = w.s1 - 1;
-    int slab = w.s0 + unit;
-    const bool any = slab < end && rb0 < rb1;
+    int slab = w.s0 + wave;
+    const bool any = slab < end;
     KFrags<T, D> kf;
     char* ks = reinterpret_cast<char*>(l_s);
     {
@@ -556,22 +554,22 @@ __global__ __launch_bounds__(kSlabThreads) void score_pass1(ScoreArgs a, SlabGri
     if (any) {
       if constexpr (PIPE) {
         i32x4 qf[SH::kNP];
-        load_q<T, D>(qlane + rb0 * kRB, qf);
+        load_q<T, D>(qlane, qf);
         f32x16 acc0 = chain<T, D, true>(qf, kf[0]), acc1;
         int turn = wave >> 2;
         for (;;) {
           take_turn(turn);
-          const int next = slab + units;
-          for (int rb = rb0; rb + 1 < rb1; ++rb) {
+          const int next = slab + kSlabWaves;
+          for (int rb = 0; rb + 1 < a.nrb; ++rb) {
             const float ms = mslane[rb * 32];
             const float l = lw[rb * 64];
             const float s = stage1<D, true>(qf, kf[1], qlane + (rb + 1) * kRB, acc1, acc0,
                                             a.scale, ms);
             lw[rb * 64] = l + (s + stage1<D, false>(qf, kf[0], nullptr, acc0, acc1, a.scale, ms));
           }
-          const int rb = rb1 - 1;
+          const int rb = a.nrb - 1;
           const float ms = mslane[rb * 32], l = lw[rb * 64];
-          const float s0 = stage1<D, true>(qf, kf[1], qlane + rb0 * kRB, acc1, acc0, a.scale, ms);
+          const float s0 = stage1<D, true>(qf, kf[1], qlane, acc1, acc0, a.scale, ms);
           // the slab's K is used up: the next slab's, behind the last tile's sums
           if (next < end) load_k<T, D>(a, kg, next, 0, kf);
           __builtin_amdgcn_sched_barrier(0);
@@ -582,7 +580,7 @@ __global__ __launch_bounds__(kSlabThreads) void score_pass1(ScoreArgs a, SlabGri
       } else {
         // kTB tiles at a time
         auto process = [&](KFrags<T, D>& k) {
-          for (int rb = rb0; rb < rb1; ++rb) {
+          for (int rb = 0; rb < a.nrb; ++rb) {
             const float ms = mslane[rb * 32];
             i32x4 qf[SH::kNP];
             load_q<T, D>(qlane + rb * kRB, qf);
@@ -596,16 +594,16 @@ __global__ __launch_bounds__(kSlabThreads) void score_pass1(ScoreArgs a, SlabGri
         };
         KFrags<T, D> kB;
         for (;;) {
-          const int nx = min(slab + units, end);
+          const int nx = min(slab + kSlabWaves, end);
           if constexpr (SH::kTB == 2) {
             load_k<T, D>(a, kg, nx, 0, kB);
             process(kf);
             loads_landed();
-            if ((slab += units) >= end) break;
-            load_k<T, D>(a, kg, min(slab + units, end), 0, kf);
+            if ((slab += kSlabWaves) >= end) break;
+            load_k<T, D>(a, kg, min(slab + kSlabWaves, end), 0, kf);
             process(kB);
             loads_landed();
-            if ((slab += units) >= end) break;
+            if ((slab += kSlabWaves) >= end) break;
           } else {
             load_k<T, D>(a, kg, slab, 1, kB);
             process(kf);
@@ -613,7 +611,7 @@ __global__ __launch_bounds__(kSlabThreads) void score_pass1(ScoreArgs a, SlabGri
             load_k<T, D>(a, kg, nx, 0, kf);
             process(kB);
             loads_landed();
-            if ((slab += units) >= end) break;
+            if ((slab += kSlabWaves) >= end) break;
           }
         }
       }
@@ -1043,18 +1041,18 @@ void launch_unrolled(const ScoreArgs& a, const SlabLaunch& p2, const SlabGrid& g
 // Few slabs for the GPU: a launch is then its start and one short chain of
 // dependent steps, and the persistent kernels' steps (window rows to LDS,
 // references, the slab loop) come one after another.  Here the waves of a
-// block have a row block each (with few row blocks, several waves share one
-// and split its tokens), whose window rows go straight into registers, and
-// K is read once through LDS.
+// block have a row block each (NW of them at most; with few row blocks,
+// several waves share one and split its tokens), whose window rows go
+// straight into registers, and K is read once through LDS.
 
 // Rows [0, n) of K from token t0 on to LDS, coalesced; n_rows rows are
 // written, those past n repeating the last.
-template <typename T, int D>
+template <typename T, int D, int NW>
 __device__ __forceinline__ void stage_rows(const ScoreArgs& a, const T* kg, int t0, int n,
                                            int n_rows, char* ks) {
   using SH = Shape<T, D>;
   constexpr int VPR = SH::kRowBytes / 16, BATCH = 8;
-  constexpr int NT = kSmallWaves * 64;
+  constexpr int NT = NW * 64;
   const int nv = n_rows * VPR;
   const char* base = reinterpret_cast<const char*>(kg + (int64_t)t0 * a.ts);
   for (int i0 = threadIdx.x; i0 < nv; i0 += BATCH * NT) {
@@ -1089,11 +1087,10 @@ __device__ __forceinline__ void load_rows(const ScoreArgs& a, const T* qg, int r
 
 // Pass 1: block (lg, chunk) of per_lg = ceil(L_p / 256) chunks; exact
 // running maxima, slab by slab.  parts waves share a row block, slab by slab.
-template <typename T, int D>
-__global__ __launch_bounds__(kSmallWaves * 64) void score_pass1_small(ScoreArgs a, int per_lg,
-                                                                      int parts) {
+template <typename T, int D, int NW>
+__global__ __launch_bounds__(NW * 64) void score_pass1_small(ScoreArgs a, int per_lg, int parts) {
   using SH = Shape<T, D>;
-  __shared__ float2 ml[kSmallWaves * 32];
+  __shared__ float2 ml[NW * 32];
   extern __shared__ __align__(16) unsigned char smem[];
   char* ks = reinterpret_cast<char*>(smem);
   const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
@@ -1104,7 +1101,7 @@ __global__ __launch_bounds__(kSmallWaves * 64) void score_pass1_small(ScoreArgs 
   const int slabs = (n + kSlab - 1) / kSlab;
   i32x4 qf[SH::kNP];
   load_rows<T, D>(a, group_q<T, D>(a, lg), rb, qf);
-  stage_rows<T, D>(a, group_k<T>(a, lg), t0, n, slabs * kSlab, ks);
+  stage_rows<T, D, NW>(a, group_k<T>(a, lg), t0, n, slabs * kSlab, ks);
   __syncthreads();
   float m = kNegBig, l = 0.f;
   const char* krow = ks + l32 * SH::kQStride + half * 16;
@@ -1151,19 +1148,18 @@ __global__ __launch_bounds__(kSmallWaves * 64) void score_pass1_small(ScoreArgs 
 }
 
 // Pass 2: block (lg, slab); the records of pass 1's division sg1.  n_out
-// outputs, of upo row blocks each.  With at most four row blocks two waves
-// share one, a tile each.
-template <typename T, int D>
-__global__ __launch_bounds__(kSmallWaves * 64) void score_pass2_small(ScoreArgs a, int S,
-                                                                      SlabGrid sg1) {
+// outputs, of upo row blocks each.  With at most half as many row blocks as
+// waves two waves share one, a tile each.
+template <typename T, int D, int NW>
+__global__ __launch_bounds__(NW * 64) void score_pass2_small(ScoreArgs a, int S, SlabGrid sg1) {
   using SH = Shape<T, D>;
-  __shared__ __align__(16) float cs[kSmallWaves * 32];
-  __shared__ float red[kSmallWaves * 64];
+  __shared__ __align__(16) float cs[NW * 32];
+  __shared__ float red[NW * 64];
   extern __shared__ __align__(16) unsigned char smem[];
   char* ks = reinterpret_cast<char*>(smem);
   const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const bool split = 2 * a.nrb <= kSmallWaves;
+  const bool split = 2 * a.nrb <= NW;
   const int part = wave / a.nrb, rb = wave - part * a.nrb;
   const int b = slab_block(), lg = b / S, slab = b - lg * S;
   const int t0 = slab * kSlab;
@@ -1173,7 +1169,7 @@ __global__ __launch_bounds__(kSmallWaves * 64) void score_pass2_small(ScoreArgs 
   i32x4 qf[SH::kNP];
   if (row < a.nrb * 32) merge_issue(a, rec, n_chunks, 0, row, pv);
   load_rows<T, D>(a, group_q<T, D>(a, lg), rb, qf);
-  stage_rows<T, D>(a, group_k<T>(a, lg), t0, min(kSlab, a.Lp - t0), kSlab, ks);
+  stage_rows<T, D, NW>(a, group_k<T>(a, lg), t0, min(kSlab, a.Lp - t0), kSlab, ks);
   if (row < a.nrb * 32) cs[row] = merge_row(a, rec, n_chunks, row, pv);
   __syncthreads();
   if (part < (split ? 2 : 1)) {
@@ -1224,17 +1220,26 @@ template <typename T, int D>
 int run_passes(const ScoreArgs& a, const SlabLaunch& p1, const SlabLaunch& p2, hipStream_t st) {
   constexpr bool kPipe = sizeof(T) == 2;   // tiles interleaved
   const size_t lds2 = pass2_lds<T, D>(a.nrb);
+  // float32 has four row blocks at most
+  constexpr int kMost = sizeof(T) == 2 ? kSmallMost : kSmallWaves;
+  const bool most = a.nrb > kSmallWaves;
   if (p1.small) {
     const size_t lds = (size_t)kSmallRows * Shape<T, D>::kQStride;
-    const int slabs = kSmallRows / kSlab, parts = kSmallWaves / a.nrb;
-    score_pass1_small<T, D><<<p1.blocks, kSmallWaves * 64, lds, st>>>(a, p1.g.per_lg,
-                                                                      parts < slabs ? parts : slabs);
+    const int slabs = kSmallRows / kSlab, parts = std::min(slabs, kSmallWaves / a.nrb);
+    if (most)
+      score_pass1_small<T, D, kMost><<<p1.blocks, kMost * 64, lds, st>>>(a, p1.g.per_lg, 1);
+    else
+      score_pass1_small<T, D, kSmallWaves><<<p1.blocks, kSmallWaves * 64, lds, st>>>(
+          a, p1.g.per_lg, parts);
   } else {
     score_pass1<T, D, kPipe><<<p1.blocks, kSlabThreads, pass1_lds<T, D>(a.nrb), st>>>(a, p1.g);
   }
-  if (p2.small)
-    score_pass2_small<T, D><<<p2.blocks, kSmallWaves * 64,
-                              (size_t)kSlab * Shape<T, D>::kQStride, st>>>(a, p2.g.S, p1.g);
+  const size_t slab_lds = (size_t)kSlab * Shape<T, D>::kQStride;
+  if (p2.small && most)
+    score_pass2_small<T, D, kMost><<<p2.blocks, kMost * 64, slab_lds, st>>>(a, p2.g.S, p1.g);
+  else if (p2.small)
+    score_pass2_small<T, D, kSmallWaves><<<p2.blocks, kSmallWaves * 64, slab_lds, st>>>(a, p2.g.S,
+                                                                                    p1.g);
   else if (a.n_out > 1 && a.W % 32 != 0)
     score_pass2<T, D, kHeadGroups, false><<<p2.blocks, kSlabThreads, lds2, st>>>(a, p2.g, p1.g);
   else

@@ -15,7 +15,8 @@ namespace starkv {
 constexpr int kSlab = 64;           // tokens per slab
 constexpr int kSlabWaves = 8;       // waves of a persistent block
 constexpr int kSmallRows = 256;     // tokens of a small-call block in pass 1
-constexpr int kSmallWaves = 8;      // row blocks (a wave each) of a small-call block at most
+constexpr int kSmallWaves = 8;      // row blocks (a wave each) of a small-call block
+constexpr int kSmallMost = 16;      // the same in the larger small-call block
 constexpr int kUnrolledBlocks = 8;  // row blocks of the unrolled pass 2 at most
 
 // Whether pass 2 runs the unrolled kernel, whose waves take whole slabs
@@ -99,17 +100,21 @@ STARKV_HD inline int slab_chunks(const SlabGrid& g, int lg) {
 //   pass 2  27/30 45/48 65/64 91/84 111/105 134/128 157/148 178/166
 // and pass 1 on 14 layers, one round of 224 blocks / two of 504, at three
 // and five frames: 38/45 62/68.
-// With at most four slabs in a block, several waves share a slab, each with
-// its part of the row blocks, where the kernel can (share).
-inline SlabLaunch slab_grid(int Lp, int nlg, int nrb, int n_cu, int max_per_lg, bool share,
-                            bool first) {
+// long_rounds: float32 keys and four row blocks, several times the matrix
+// time per round, so that a start is a smaller part of one (14 layers of 4
+// groups, d = 64, 13,679 tokens: 253 us of the call with the other start,
+// 224 blocks per pass, 240 with this one, 504; 8,297 tokens 160 and 162).
+// In a block of at most `share` slabs several waves share a slab, each with
+// its part of the row blocks.
+inline SlabLaunch slab_grid(int Lp, int nlg, int nrb, int n_cu, int max_per_lg, int share,
+                            bool long_rounds, bool first) {
   SlabLaunch l;
   SlabGrid& g = l.g;
   g.S = (Lp + kSlab - 1) / kSlab;
-  const int start = first ? 10 : 8;
+  const int start = long_rounds ? 4 : first ? 10 : 8;
   auto waves_per_slab = [&](int64_t slabs) {
     int rs = 1;
-    while (share && rs * 2 * slabs <= kSlabWaves && rs * 2 <= nrb) rs *= 2;
+    while (slabs <= share && rs * 2 * slabs <= kSlabWaves && rs * 2 <= nrb) rs *= 2;
     return rs;
   };
   auto rounds8 = [&](int64_t slabs) {
@@ -121,10 +126,13 @@ inline SlabLaunch slab_grid(int Lp, int nlg, int nrb, int n_cu, int max_per_lg, 
   int64_t best = -1;
   const int64_t p_max = std::min<int64_t>({(int64_t)max_per_lg, (int64_t)g.S,
                                            std::max<int64_t>(1, 4L * n_cu / nlg)});
-  for (int64_t p = 1; p <= p_max; ++p) {
+  // of the block counts that run in k rounds on the CUs the largest costs
+  // least; among equal costs the fewest rounds, though not fewer slabs
+  for (int k = 1; k <= 4; ++k) {
+    const int64_t p = std::min<int64_t>(p_max, std::max<int64_t>(1, (int64_t)k * n_cu / nlg));
     const int64_t q = (g.S + p - 1) / p;
     const int64_t cost = (p * nlg + n_cu - 1) / n_cu * (rounds8(q) + start);
-    if (best < 0 || cost <= best) {
+    if (best < 0 || cost < best) {
       best = cost;
       g.per_lg = (int)p;
       g.q = (int)(g.S / p);
@@ -153,31 +161,48 @@ inline SlabLaunch slab_grid(int Lp, int nlg, int nrb, int n_cu, int max_per_lg, 
 
 // The two passes' launches for n_layers * G groups of nrb row blocks, at most
 // max_chunks records per group in the workspace.  one_sum: one output per
-// group (waves may then share a slab in pass 2, but not in its unrolled
-// kernel); whole_blocks: an output's rows are whole row blocks.
+// group; whole_blocks: an output's rows are whole row blocks.
+//
+// Waves share a slab only in pass 2 with one sum per group, outside the
+// unrolled kernel, at most two slabs, and where a slab is long work for a
+// wave: float32 keys, or more than ten row blocks.  us of the call, shared /
+// not: float32, d = 64, 4 row blocks, 376 slabs on 256 CUs 32.9 / 33.6; bf16,
+// 14 row blocks, d = 128, 376 slabs 30.3 / 30.3, 752 slabs 31.8 / 31.0, d =
+// 64, 376 slabs 24.0 / 24.5; 9 row blocks, 376 slabs 26.6 / 25.3; pass 1, 9
+// row blocks, 564 slabs 27.2 / 26.3.
 //
 // The small-call kernels run one short step per block and win while the
-// blocks run side by side: pass 1 (a block per CU fits beside another, but
-// slower) up to one block per CU, pass 2 up to one and a half, or one with
-// fewer than four row blocks (368 blocks: 7.9 / 8.4 at four row blocks, 7.6
-// / 6.7 at two, 7.3 / 5.5 at one).  28 heads on
-// 4 groups, d = 128, us per launch, small against persistent: pass 1 at 192
-// blocks 8.0 / 11.0, 240 and 264 blocks 13.5 / 11.5, 288 blocks 13.0 / 11.2;
-// pass 2 at 184 blocks 6.1 / 7.9, 368 blocks 8.8 / 9.3, 528 blocks 11.1 / 9.8.
+// blocks run side by side.  Pass 1 up to one block per CU: 28 heads on 4
+// groups, d = 128, us of the call with it / with the persistent pass 1: 96
+// blocks 19.7 / 22.2, 240 blocks 20.1 / 22.6, 260 blocks 26.3 / 23.8, 308
+// blocks 27.3 / 24.7; with 14 row blocks 48 blocks 28.0 / 28.8, d = 64 22.0 /
+// 23.3, but with 9 row blocks 24.9 / 24.1 and with 11 25.9 / 26.1.  Pass 2
+// likewise (220 blocks 17.1 / 18.2, 264 blocks 19.0 / 18.3; 14 row blocks,
+// 188 blocks 26.8 / 28.8, 376 blocks 33.8 / 29.9).  Up to eight row blocks it
+// wins to one and a half blocks per CU for bf16 keys with d = 64 and several
+// row blocks (460 blocks 16.4 / 17.0), an output per head (440 blocks 27.5 /
+// 28.0) or four row blocks of float32 keys (376 blocks 27.6 / 29.0); it does
+// not with one or two row blocks of bf16 keys and d = 128 (220 blocks 13.5 /
+// 12.8), whose persistent kernel starts as soon.
 inline void slab_launches(int Lp, int nlg, int nrb, int n_cu, int max_chunks, bool one_sum,
                           bool whole_blocks, int d, int esz, SlabLaunch* p1,
                           SlabLaunch* p2) {
   const bool unrolled = pass2_unrolled(d, esz, nrb, whole_blocks);
-  *p1 = slab_grid(Lp, nlg, nrb, n_cu, max_chunks, true, true);
-  *p2 = slab_grid(Lp, nlg, nrb, n_cu, 1 << 30, one_sum && !unrolled, false);
-  if (nrb > kSmallWaves) return;
+  const int share = !one_sum || unrolled ? 0 : esz == 4 || nrb > 10 ? 2 : 0;
+  const bool long_rounds = esz == 4 && nrb >= 4;
+  *p1 = slab_grid(Lp, nlg, nrb, n_cu, max_chunks, 0, long_rounds, true);
+  *p2 = slab_grid(Lp, nlg, nrb, n_cu, 1 << 30, share, long_rounds, false);
   const int64_t chunks = (Lp + kSmallRows - 1) / kSmallRows;
-  if (chunks <= max_chunks && chunks * nlg <= n_cu) {
+  if (chunks <= max_chunks && chunks * nlg <= n_cu &&
+      (nrb <= kSmallWaves || nrb > 11 || d == 64)) {
     p1->small = true;
     p1->g.per_lg = (int)chunks;
     p1->blocks = (int)(chunks * nlg);
   }
-  const int64_t p2_small = nrb >= 4 ? n_cu + n_cu / 2 : n_cu;
+  int p2_small = n_cu;
+  if (nrb <= kSmallWaves && (esz == 4 ? nrb >= 4 : d == 64 ? nrb >= 2 : nrb > 4 && !one_sum))
+    p2_small += n_cu / 2;
+  if (esz == 2 && d == 128 && nrb <= 2) p2_small = 0;
   if (whole_blocks && (int64_t)p2->g.S * nlg <= p2_small) {
     p2->small = true;
     p2->blocks = p2->g.S * nlg;

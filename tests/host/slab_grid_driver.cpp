@@ -1,7 +1,8 @@
 // Checks the scoring passes' division of slabs into blocks (slab_grid.h, the
 // same source the library compiles) for each "Lp nlg nrb n_cu max_chunks
-// one_sum whole_blocks [d element-bytes]" line of stdin: prints "ok", or what is wrong, the
-// two passes' kinds and their block counts.
+// one_sum whole_blocks [d element-bytes]" line of stdin: prints "ok", or what
+// is wrong, the two passes' kinds, their block counts and the waves that share
+// a slab in pass 2.
 #include <cstdio>
 #include <string>
 #include <vector>
@@ -56,9 +57,11 @@ int main() {
     if (!bad && !one && p2.g.rs != 1) bad = "shared slabs with several outputs";
     if (!bad && pass2_unrolled(d, esz, nrb, whole != 0) && p2.g.rs != 1)
       bad = "shared slabs in the unrolled kernel";
-    std::printf("%s %s %s %d %d\n", bad ? bad : "ok",
+    if (!bad && p1.g.rs != 1) bad = "shared slabs in pass 1";
+    std::printf("%s %s %s %d %d %d\n", bad ? bad : "ok",
                 p1.small ? "small" : p1.g.per_lg ? "aligned" : "crossing",
-                p2.small ? "small" : p2.g.per_lg ? "aligned" : "crossing", p1.blocks, p2.blocks);
+                p2.small ? "small" : p2.g.per_lg ? "aligned" : "crossing", p1.blocks, p2.blocks,
+                p2.g.rs);
   }
   return 0;
 }

@@ -183,7 +183,7 @@ def test_scoring_slab_division(tmp_path):
         assert {o.split()[p] for o in out} == {"small", "aligned", "crossing"}
 
 
-def _launches(tmp_path, lines):
+def _launches(tmp_path, lines, full=False):
     exe = _build(tmp_path, "slab_grid", [os.path.join(HOST, "slab_grid_driver.cpp")],
                  sanitize=False)
     r = subprocess.run([exe], input="".join(" ".join(map(str, x)) + "\n" for x in lines),
@@ -191,7 +191,7 @@ def _launches(tmp_path, lines):
     assert r.returncode == 0, r.stderr
     out = [line.split() for line in r.stdout.splitlines()]
     assert all(o[0] == "ok" for o in out) and len(out) == len(lines)
-    return [(o[1], o[2], int(o[3]), int(o[4])) for o in out]
+    return [(o[1], o[2], *map(int, o[3:6 if full else 5])) for o in out]
 
 
 def test_scoring_division_between_frame_counts(tmp_path):
@@ -230,11 +230,85 @@ def _form_launches(tmp_path, forms):
         one = not per_head or H == G
         lines.append((Lp, nl * G, -(-W * (H // G) // 32), 256, -(-Lp // 256), int(one),
                       int(one or W % 32 == 0), d, 4 if dtype == "f32" else 2))
-    return [g[:2] for g in _launches(tmp_path, lines)]
+    return [(*g[:2], g[4]) for g in _launches(tmp_path, lines, full=True)]
 
 
 def test_score_forms_cross_groups(tmp_path):
     """The shapes that the GPU tests of crossing blocks use give crossing
     blocks in both passes."""
     from tests.test_score_paths_gpu import CROSSING
-    assert set(_form_launches(tmp_path, CROSSING)) == {("crossing", "crossing")}
+    assert set(_form_launches(tmp_path, CROSSING)) == {("crossing", "crossing", 1)}
+
+
+def test_scoring_launch_rules(tmp_path):
+    """Which launches take the small-call kernels and where waves share a
+    slab, on both sides of every line drawn by timing, on 256 CUs."""
+    form = lambda Lp, nlg, nrb, d, esz, one=1: (Lp, nlg, nrb, 256, -(-Lp // 256), one, 1, d, esz)
+    cases = [   # (case, pass 1, pass 2, waves per slab of pass 2)
+        (form(2915, 4, 7, 128, 2), "small", "small", None),       # 48 chunks, 184 slabs
+        (form(2915, 8, 7, 128, 2), "small", "aligned", 1),        # 368 slabs
+        (form(2915, 8, 7, 128, 2, 0), "small", "small", None),
+        (form(2915, 8, 4, 128, 2, 0), "small", "aligned", 1),
+        (form(2915, 8, 7, 64, 2), "small", "small", None),
+        (form(2915, 12, 7, 64, 2), "small", "aligned", 1),
+        (form(2915, 8, 1, 64, 2), "small", "aligned", 1),
+        (form(700, 4, 2, 128, 2), "small", "aligned", 1),
+        (form(700, 4, 3, 128, 2), "small", "small", None),
+        (form(256 * 64, 4, 7, 128, 2), "small", "aligned", 1),    # 256 chunks
+        (form(256 * 64 + 1, 4, 7, 128, 2), "aligned", "aligned", 1),
+        (form(2915, 4, 14, 128, 2), "small", "small", None),
+        (form(2915, 8, 14, 128, 2), "small", "aligned", 4),       # two slabs per block
+        (form(2915, 12, 14, 128, 2), "small", "aligned", 1),      # three
+        (form(2915, 4, 9, 128, 2), "aligned", "small", None),
+        (form(2915, 8, 9, 128, 2), "aligned", "aligned", 1),
+        (form(2915, 8, 9, 64, 2), "small", "aligned", 1),
+        (form(2915, 8, 4, 64, 4), "small", "small", None),
+        (form(2915, 8, 2, 64, 4), "small", "aligned", 2),
+        (form(2915, 12, 2, 64, 4), "small", "aligned", 1),
+    ]
+    got = _launches(tmp_path, [c for c, *_ in cases], full=True)
+    for (c, a, b, rs), g in zip(cases, got):
+        assert (g[0], g[1]) == (a, b) and rs in (None, g[4]), (c, g)
+
+
+def _aligned_blocks(S, nlg, n_cu, p_max, first, start):
+    """Blocks per group of the cheapest aligned division, every count tried."""
+    best = None
+    for p in range(1, p_max + 1):
+        q = -(-S // p)
+        rounds = -(-p * nlg // n_cu)
+        cost = rounds * (-(-(q - first) // 8) * 8 + start)
+        if best is None or (cost, rounds, -p) < best[0]:
+            best = ((cost, rounds, -p), p)
+    return best[1]
+
+
+def test_scoring_division_tries_the_counts_that_matter(tmp_path):
+    """The division looks at four block counts per group, the largest of each
+    number of rounds; the cheapest of all counts is among them."""
+    lines, want = [], []
+    for Lp in (1025, 2915, 5606, 8297, 13679, 40845):
+        for nlg in (20, 40, 56, 90, 112, 200, 256, 300, 600, 1200):
+            S, mc = -(-Lp // 64), -(-Lp // 256)
+            lim = max(1, 4 * 256 // nlg)
+            lines.append((Lp, nlg, 7, 256, mc, 1, 1, 128, 2))
+            want.append((_aligned_blocks(S, nlg, 256, min(mc, S, lim), 1, 10),
+                         _aligned_blocks(S, nlg, 256, min(S, lim), 0, 8)))
+    seen = 0
+    for x, w, g in zip(lines, want, _launches(tmp_path, lines, full=True)):
+        for i in (0, 1):
+            if g[i] == "aligned":
+                assert g[2 + i] == w[i] * x[1], (x, i, w, g)
+                seen += 1
+    assert seen > 60, seen
+
+
+def test_score_row_blocks_take_their_kernels(tmp_path):
+    """The GPU tests of every row-block count and of shared slabs launch the
+    kernels they name: the persistent ones, or the small-call ones."""
+    from tests.test_score_paths_gpu import ROW_BLOCKS, SHARED, SMALL_ROW_BLOCKS
+    for a, b, _ in _form_launches(tmp_path, ROW_BLOCKS):
+        assert "small" not in (a, b)
+    small = _form_launches(tmp_path, SMALL_ROW_BLOCKS)
+    assert {f[1] for f in small} == {"small"} and {f[0] for f in small} == {"small", "aligned"}
+    assert [f[1:] for f in _form_launches(tmp_path, SHARED)] == [("aligned", 4), ("aligned", 2)]

@@ -325,8 +325,8 @@ def test_token_tail_sweep(Lp):
 @pytest.mark.parametrize("nrb,per_head", [(n, False) for n in range(1, 15)]
                          + [(n, True) for n in range(2, 15)])
 def test_slab_row_block_sweep(nrb, per_head):
-    """Every row-block count of the persistent pass-2 kernel (bf16, d = 128):
-    with a subspace per group, W = 32*nrb - 8 rows of one head (a padded last
+    """Every row-block count at a call of few slabs, whose pass 2 (and pass 1,
+    but for 9 to 11 row blocks) is the small-call kernel (bf16, d = 128): with a subspace per group, W = 32*nrb - 8 rows of one head (a padded last
     row block); with a subspace per head, nrb >= 2 heads of W = 32 rows (one
     row block each, one output per stage; one head per group is the
     per-group case).  L_p = 300: four full 64-token slabs

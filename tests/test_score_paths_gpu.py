@@ -1,6 +1,8 @@
 """The scoring passes' launch forms against a 64-bit softmax: small-call
 kernels, aligned and crossing persistent blocks, slabs shared by waves, every
-output layout, and row sums that leave the range of a block's reference."""
+row-block count and output layout, and row sums that leave the range of a
+block's reference.  A host test checks that the forms named here launch the
+kernels they name."""
 
 from __future__ import annotations
 
@@ -60,13 +62,13 @@ FORMS = [
     (1, 8, 2, 128, 32, 321, "f32", False),        # small, fp32
     (1, 8, 2, 128, 32, 321, "bf16", True),        # small, per head
     (1, 8, 2, 128, 16, 321, "bf16", True),        # small pass 1, 8-row heads in pass 2
-    (40, 14, 2, 64, 32, 700, "bf16", False),      # aligned, slabs shared by waves
+    (40, 14, 2, 64, 32, 700, "bf16", False),      # small pass 1, aligned pass 2
     (28, 28, 4, 128, 32, 1025, "bf16", False),    # aligned
     (28, 28, 4, 128, 32, 1025, "bf16", True),
     (28, 12, 2, 128, 24, 1025, "bf16", True),     # 8-row heads that cross row blocks
     (3, 2, 2, 64, 512, 14001, "bf16", False),     # sixteen row blocks, few groups
-    (1, 15, 1, 128, 32, 30001, "bf16", False),    # fifteen row blocks, persistent
-    (11, 32, 8, 64, 16, 9001, "bf16", False),     # ranges crossing groups
+    (1, 15, 1, 128, 32, 30001, "bf16", False),    # fifteen row blocks, small pass 1
+    (11, 32, 8, 64, 16, 9001, "bf16", False),     # aligned pass 1, pass 2 crossing groups
     (9, 16, 4, 128, 8, 9001, "f32", False),       # fp32, one 32-token tile at a time
     (9, 16, 4, 64, 8, 9001, "f32", True),
 ]
@@ -174,3 +176,25 @@ def test_crossing_blocks(form, at):
     before the cache's end, the sums are redone in segments that other
     segments of the same block follow."""
     _run(*form, spike=24.0 if at else 0.0, at=at and form[5] + at)
+
+
+# every row-block count of the persistent kernels: 44 groups of 21 slabs, the
+# last ragged; W = 32 nrb - 8 rows of one head per group (a padded last row
+# block), or nrb heads of 32 rows with an output each
+ROW_BLOCKS = [(11, 4, 4, 128, 32 * n - 8, 1313, "bf16", False) for n in range(1, 16)] + \
+             [(11, 4 * n, 4, 128, 32, 1313, "bf16", True) for n in range(2, 16)]
+# and of the larger small-call kernels (nine row blocks and more)
+SMALL_ROW_BLOCKS = [(1, 2, 2, d, 32 * n - 8, 321, "bf16", False)
+                    for d, n in ((128, 9), (128, 12), (128, 15), (64, 9), (64, 16))] + \
+                   [(1, 2 * n, 2, d, 32, 321, "bf16", True)
+                    for d, n in ((128, 9), (128, 12), (128, 15), (64, 9), (64, 16))]
+
+
+# pass 2's waves share a slab, four and two of them
+SHARED = [(2, 28, 4, 128, 64, 2915, "bf16", False), (2, 8, 4, 64, 32, 2915, "f32", False)]
+
+
+@pytest.mark.parametrize("form", ROW_BLOCKS + SMALL_ROW_BLOCKS + SHARED,
+                         ids=["-".join(map(str, f)) for f in ROW_BLOCKS + SMALL_ROW_BLOCKS + SHARED])
+def test_row_blocks(form):
+    _run(*form, spike=0.0)
