@@ -93,7 +93,7 @@ struct StatsArgs {
 
 constexpr int kBatch = 8;                 // loads in flight per thread
 constexpr int kKeyBatch = 8;              // keys per thread per rank-binning step
-constexpr int kFuse = 4;                  // keys per thread per step of the fused pass
+constexpr int kFuse = 4;                  // keys per thread per step of the fused pass (few: 2)
 constexpr int kLoadBatch = 16;            // loads in flight in the first pass over S
 constexpr int kDirect = 256;              // candidates ranked directly, no more digits
 constexpr int kTieChunks = 256;           // visual-index chunks for locating tie splits
@@ -184,8 +184,18 @@ __device__ __forceinline__ void stats_block(const StatsArgs& a, int* layer, int*
   }
 }
 
-// CACHED: the visual keys fit the block shape's key cache.
-template <int NT, bool CACHED>
+// Where the MI passes find the visual keys, and how many there are.
+enum KeyPlace {
+  kInMemory,   // read from S in every pass
+  kInLds,      // N <= kKeyCache
+  kFewInLds,   // N <= few_keys<NT>(): no histogram copies or cell table, short batches
+};
+template <int NT>
+constexpr int few_keys() {
+  return 8 * NT < StatsShape<NT>::kKeyCache ? 8 * NT : StatsShape<NT>::kKeyCache;
+}
+
+template <int NT, KeyPlace KEYS>
 __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g) {
   constexpr int kThreads = NT, kWaves = NT / 64;
   constexpr int kHistInts = StatsShape<NT>::kHistInts, kKeyCache = StatsShape<NT>::kKeyCache,
@@ -373,7 +383,8 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
   const int K = a.nbins;
   const int M = a.grid;
   const int ncell = M * M;
-  constexpr bool cached = CACHED;   // N <= kKeyCache
+  constexpr bool cached = KEYS != kInMemory, few = KEYS == kFewInLds;
+  constexpr int kBinKeys = few ? 2 : kFuse;
   // Candidates (keys in the edges' first-digit buckets): the fused pass
   // keeps (key, cell << 24 | visual index) pairs, the compaction pass keys
   // only; in the candidate area while the keys are cached, else in the key
@@ -729,7 +740,7 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
           const int cells = K * ncell, cstride = cells + 9;
           int* const extra = NT == 1024 ? jh + cells + 9 : hist + kFirstDigitBins / 2;
           const int room = NT == 1024 ? kHistInts - kJointOff - cells - 9 : kFirstDigitBins / 2;
-          const int fit = N >= 4 * kThreads ? room / cstride : 0;
+          const int fit = !few && N >= 4 * kThreads ? room / cstride : 0;
           const int ncopy = fit >= 7 ? 8 : fit >= 3 ? 4 : fit >= 1 ? 2 : 1;
           const int copy = lane & (ncopy - 1);
           int* const jl = copy == 0 ? jh : extra + (copy - 1) * cstride;
@@ -743,10 +754,10 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
           // and its candidate segment above that
           uint16_t* const d_lut = reinterpret_cast<uint16_t*>(hist);
           for (int dd = tid; dd < nb; dd += kThreads) {
-            const bool edge = (bucket_bits[dd >> 5] >> (dd & 31)) & 1u;
-            d_lut[dd] = (uint16_t)(edge ? 0x100 | (seg_of_bucket((uint32_t)dd) << 9)
-                                        : lower_edges((uint32_t)dd));
+            if (!((bucket_bits[dd >> 5] >> (dd & 31)) & 1u))
+              d_lut[dd] = (uint16_t)lower_edges((uint32_t)dd);
           }
+          if (tid < n_seg) d_lut[seg_dg[tid]] = (uint16_t)(0x100 | (tid << 9));
           for (int i = tid; i < (ncopy - 1) * cstride; i += kThreads) extra[i] = 0;
           // Cells of a frame's tokens, a byte each, when every span has the
           // same shape and the table fits: behind the histogram's copies in
@@ -758,7 +769,7 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
           const int tab_bytes = NT == 1024 ? 4 * (room - (ncopy - 1) * cstride)
                                            : (cached ? 0 : 4 * kCand);
           const int frame = a.sp.off[1];
-          const bool tabled = a.sp.same && a.sp.n > 1 && frame <= tab_bytes;
+          const bool tabled = !few && a.sp.same && a.sp.n > 1 && frame <= tab_bytes;
           if (tabled) {
             const float rc = __builtin_amdgcn_rcpf((float)sp_cols[0]);
             const float fr = (float)M * __builtin_amdgcn_rcpf((float)sp_rows[0]);
@@ -770,7 +781,7 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
             }
           }
           __syncthreads();
-          // kFuse keys of a thread at a time (visual indices i0 + u *
+          // kBinKeys keys of a thread at a time (visual indices i0 + u *
           // kThreads, the first n valid): all their table reads, then all
           // their histogram adds and slot requests, then the candidates'
           // writes, so that a step's LDS latencies overlap instead of
@@ -780,19 +791,19 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
           // layers) and 8.9 us at 13,455 (4 on 28 layers, keys in LDS); now
           // 46, 23 and 7.0.  Reading S bounds the first of them: a CU gets
           // about 25 bytes a ns, each pass over the keys 22 us.
-          auto fuse = [&](int i0, int n, const uint32_t (&kv)[kFuse], const int (&cell)[kFuse]) {
-            int lut[kFuse], pos[kFuse];
+          auto fuse = [&](int i0, int n, const uint32_t (&kv)[kBinKeys], const int (&cell)[kBinKeys]) {
+            int lut[kBinKeys], pos[kBinKeys];
 #pragma unroll
-            for (int u = 0; u < kFuse; ++u)
+            for (int u = 0; u < kBinKeys; ++u)
               lut[u] = d_lut[(kv[u] >> shift) & (uint32_t)(nb - 1)];
 #pragma unroll
-            for (int u = 0; u < kFuse; ++u)
+            for (int u = 0; u < kBinKeys; ++u)
               if (u < n && !(lut[u] & 0x100)) atomicAdd(&jl[lut[u] * ncell + cell[u]], 1);
 #pragma unroll
-            for (int u = 0; u < kFuse; ++u)
+            for (int u = 0; u < kBinKeys; ++u)
               if (u < n && (lut[u] & 0x100)) pos[u] = atomicAdd(&seg_cur[lut[u] >> 9], 1);
 #pragma unroll
-            for (int u = 0; u < kFuse; ++u)
+            for (int u = 0; u < kBinKeys; ++u)
               if (u < n && (lut[u] & 0x100)) {
                 ck[pos[u]] = kv[u];
                 cv[pos[u]] = ((uint32_t)cell[u] << 24) | (uint32_t)(i0 + u * kThreads);
@@ -809,11 +820,11 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
               const int dq = small_quot(kThreads, cols, rc), dr = kThreads - dq * cols;
               int r = small_quot(tid, cols, rc);
               int c = tid - r * cols;
-              for (int i0 = a.sp.off[sp] + tid; i0 < end; i0 += kFuse * kThreads) {
-                uint32_t kv[kFuse];
-                int cell[kFuse];
+              for (int i0 = a.sp.off[sp] + tid; i0 < end; i0 += kBinKeys * kThreads) {
+                uint32_t kv[kBinKeys];
+                int cell[kBinKeys];
 #pragma unroll
-                for (int u = 0; u < kFuse; ++u) {
+                for (int u = 0; u < kBinKeys; ++u) {
                   const int i = i0 + u * kThreads;
                   kv[u] = 0u;
                   cell[u] = 0;
@@ -828,38 +839,38 @@ __device__ __forceinline__ void stats_body(const StatsArgs& a, int layer, int g)
                 fuse(i0, (end - i0 + kThreads - 1) / kThreads, kv, cell);
               }
             }
-          } else {        // cached: keys in LDS; else kSub * kFuse loads in flight
+          } else {        // cached: keys in LDS; else kSub * kBinKeys loads in flight
             constexpr int kSub = 2;
-            auto load = [&](int i0, uint32_t (&kw)[kSub * kFuse]) {
+            auto load = [&](int i0, uint32_t (&kw)[kSub * kBinKeys]) {
               if (cached) {
 #pragma unroll
-                for (int u = 0; u < kSub * kFuse; ++u)
+                for (int u = 0; u < kSub * kBinKeys; ++u)
                   kw[u] = i0 + u * kThreads < N ? kc[i0 + u * kThreads] : 0u;
               } else {
-                float v[kSub * kFuse];
+                float v[kSub * kBinKeys];
 #pragma unroll
-                for (int u = 0; u < kSub * kFuse; ++u) {
+                for (int u = 0; u < kSub * kBinKeys; ++u) {
                   const int i = i0 + u * kThreads;
                   v[u] = i < N ? Sg[token_of(i)] : 0.f;
                 }
 #pragma unroll
-                for (int u = 0; u < kSub * kFuse; ++u) kw[u] = fkey(v[u]);
+                for (int u = 0; u < kSub * kBinKeys; ++u) kw[u] = fkey(v[u]);
               }
             };
             // cell_of(i): the cells of this thread's indices, in order
             auto walk = [&](auto cell_of) {
-              for (int i0 = tid; i0 < N; i0 += kSub * kFuse * kThreads) {
-                uint32_t kw[kSub * kFuse];
+              for (int i0 = tid; i0 < N; i0 += kSub * kBinKeys * kThreads) {
+                uint32_t kw[kSub * kBinKeys];
                 load(i0, kw);
 #pragma unroll
                 for (int w = 0; w < kSub; ++w) {
-                  const int j0 = i0 + w * kFuse * kThreads;
+                  const int j0 = i0 + w * kBinKeys * kThreads;
                   if (j0 >= N) break;
-                  uint32_t kv[kFuse];
-                  int cell[kFuse];
+                  uint32_t kv[kBinKeys];
+                  int cell[kBinKeys];
 #pragma unroll
-                  for (int u = 0; u < kFuse; ++u) {
-                    kv[u] = kw[w * kFuse + u];
+                  for (int u = 0; u < kBinKeys; ++u) {
+                    kv[u] = kw[w * kBinKeys + u];
                     cell[u] = cell_of(j0 + u * kThreads);
                   }
                   fuse(j0, (N - j0 + kThreads - 1) / kThreads, kv, cell);
@@ -1209,7 +1220,7 @@ __device__ __forceinline__ void finalize_layer(const FinalArgs& a, int layer, in
 // With SEL, the block that runs a layer's finalize then runs that layer's
 // selection (select_body) in the same workgroup, its LDS carved from the
 // statistics' dynamic LDS, which no longer holds anything live by then.
-template <int NT, bool SEL, bool CACHED>
+template <int NT, bool SEL, KeyPlace KEYS>
 __global__ __launch_bounds__(NT, NT == 1024 ? 1 : 4) void stats_kernel(StatsArgs a, SelArgs sel) {
   static_assert(!SEL || NT == kSelThreads, "the selection body needs a 1024-thread block");
   __shared__ int last_s;
@@ -1227,7 +1238,7 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 1 : 4) void stats_kernel(StatsArgs
     for (int i = threadIdx.x; i < a.sc; i += NT)
       a.scal[(size_t)layer * a.sc + i] = __builtin_nanf("");
   } else {
-    stats_body<NT, CACHED>(a, layer, g);
+    stats_body<NT, KEYS>(a, layer, g);
     // Lanes of wave 0 wrote every value the finalize and a fused selection
     // read from this block (MI_g or H^ by thread 0, phi by the first four
     // lanes); thread 0's fence, in that wave, publishes them before it
@@ -1327,9 +1338,9 @@ StatsArgs make_stats_args(const Geometry& g, const starkv_params& p, const float
   return a;
 }
 
-template <int NT, bool SEL, bool CACHED>
+template <int NT, bool SEL, KeyPlace KEYS>
 void raise_lds_limit() {
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&stats_kernel<NT, SEL, CACHED>),
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&stats_kernel<NT, SEL, KEYS>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)stats_lds<NT>());
 }
 
@@ -1337,30 +1348,42 @@ void raise_lds_limit() {
 // once per process (function-local static initialisation is thread-safe).
 void raise_lds_limits() {
   static const bool raised = [] {
-    raise_lds_limit<1024, true, true>();
-    raise_lds_limit<1024, true, false>();
-    raise_lds_limit<1024, false, true>();
-    raise_lds_limit<1024, false, false>();
-    raise_lds_limit<512, false, true>();
-    raise_lds_limit<512, false, false>();
+    raise_lds_limit<1024, true, kInMemory>();
+    raise_lds_limit<1024, true, kInLds>();
+    raise_lds_limit<1024, true, kFewInLds>();
+    raise_lds_limit<1024, false, kInMemory>();
+    raise_lds_limit<1024, false, kInLds>();
+    raise_lds_limit<1024, false, kFewInLds>();
+    raise_lds_limit<512, false, kInMemory>();
+    raise_lds_limit<512, false, kInLds>();
+    raise_lds_limit<512, false, kFewInLds>();
     return true;
   }();
   (void)raised;
 }
 
-// The keys are kept in LDS by one kernel and read from S in every pass by
-// another.  With both forms in one, calls of one frame paid for the other's
-// registers and instruction fetches: one frame of 28 layers of 4 groups 34.4
-// us against 34.0 apart, five frames 49.7 against 48.6, a subspace per head
-// at twelve frames 127 against 120.
+// A kernel for each key place.  With the LDS and memory forms in one, calls
+// of one frame paid for the other's registers and instruction fetches: one
+// frame of 28 layers of 4 groups 34.4 us against 34.0 apart, five frames 49.7
+// against 48.6, a subspace per head at twelve frames 127 against 120.  The
+// histogram copies and the cell table cost a call of few keys more than they
+// save: us of the fused call with and without them, one layer of 4 groups,
+// 1,196 keys 30.5 / 29.0, 4,641 keys 35.2 / 33.8, 6,000 keys 37.9 / 35.8,
+// 7,700 keys 39.7 / 38.0; five spans of 1,196 keys 37.7 either way.
+template <int NT, bool SEL, KeyPlace KEYS>
+void run_stats(const StatsArgs& a, const SelArgs& sel, hipStream_t st) {
+  const int blocks = (stats_layer_blocks(a.G) + a.n_ent - 1) * a.n_layers;
+  stats_kernel<NT, SEL, KEYS><<<blocks, NT, stats_lds<NT>(), st>>>(a, sel);
+}
+
 template <int NT, bool SEL>
 int launch_stats(const StatsArgs& a, const SelArgs& sel, hipStream_t st) {
   raise_lds_limits();
-  const int blocks = (stats_layer_blocks(a.G) + a.n_ent - 1) * a.n_layers;
-  if (a.sp.off[a.sp.n] <= StatsShape<NT>::kKeyCache)
-    stats_kernel<NT, SEL, true><<<blocks, NT, stats_lds<NT>(), st>>>(a, sel);
-  else
-    stats_kernel<NT, SEL, false><<<blocks, NT, stats_lds<NT>(), st>>>(a, sel);
+  constexpr int kCache = StatsShape<NT>::kKeyCache;
+  const int n = a.sp.off[a.sp.n];
+  if (n <= few_keys<NT>()) run_stats<NT, SEL, kFewInLds>(a, sel, st);
+  else if (n > kCache) run_stats<NT, SEL, kInMemory>(a, sel, st);
+  else if constexpr (few_keys<NT>() < kCache) run_stats<NT, SEL, kInLds>(a, sel, st);
   return (int)hipGetLastError();
 }
 

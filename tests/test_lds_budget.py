@@ -79,9 +79,9 @@ def test_stats_kernel_lds_fits(tmp_path):
 @needs_hipcc
 def test_stats_kernels_use_no_scratch(tmp_path):
     """Every form of the statistics kernel (three block shapes, with and
-    without the selection, visual keys in LDS or read from memory) keeps its
-    values in registers: scratch memory is set up and touched also by calls
-    whose own pass needs none of it.  Each form's LDS fits as above."""
+    without the selection, visual keys in LDS, few or more, or read from
+    memory) keeps its values in registers: scratch memory is set up and touched
+    also by calls whose own pass needs none of it.  Each form's LDS fits as above."""
     path = os.path.join(B.CSRC, "state.hip")
     src = open(path).read()
     out = tmp_path / "state.s"

@@ -385,7 +385,10 @@ def test_fused_binning_forms(form):
 
 # visual tokens at the key cache's size and one past it, of the wide, the
 # narrow and the small block shape (the last two: a subspace per head)
+# and of the few keys that are binned without histogram copies
 CACHE_EDGES = [
+    (1, 64, 128, 0, False, 8, 8), (1, 3, 2731, 0, False, 8, 8), (2, 64, 64, 3, False, 16, 16),
+    (1, 64, 64, 0, True, 12, 8), (1, 17, 241, 0, True, 12, 8),
     (1, 128, 160, 0, False, 8, 8), (1, 3, 6827, 0, False, 8, 8), (1, 64, 96, 0, True, 12, 8),
     (1, 5, 1229, 0, True, 12, 8), (1, 32, 64, 0, True, 8, 8), (1, 3, 683, 0, True, 8, 8),
 ]
@@ -393,8 +396,8 @@ CACHE_EDGES = [
 
 @pytest.mark.parametrize("form", CACHE_EDGES, ids=["-".join(map(str, f)) for f in CACHE_EDGES])
 def test_key_cache_edges(form):
-    """The kernel that keeps the keys in LDS and the one that reads them from
-    S, on both sides of every shape's limit."""
+    """The kernels that keep few keys or more in LDS and the one that reads
+    them from S, on both sides of every shape's limits."""
     test_fused_binning_forms(form)
 
 
