@@ -12,8 +12,8 @@ namespace starkv {
 
 // Largest window-row block per group kept in LDS by the scoring kernels.
 constexpr int kMaxQBytes = 128 * 1024;
-// Token chunk of one scoring workgroup: the smallest size sets the
-// workspace bound, the launcher may pick larger chunks.
+// The scoring workspace holds ceil(L_p / kMinChunk) records of row statistics
+// per (layer, group): at most that many blocks of pass 1 have slabs of one.
 constexpr int kMinChunk = 256;
 constexpr int kMaxL = 1 << 26;
 

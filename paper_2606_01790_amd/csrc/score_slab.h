@@ -38,8 +38,8 @@
 // groups, 32 rows: 73 us against 63 at 5,606 tokens, 172 against 162 at
 // 13,679; 32 layers of 8 groups, 128 rows: 82 against 73 at 5,606).  Against
 // a pass 1 with K tiles in LDS and a wave per row block, one fragment read
-// per MFMA: 2209 -> 1772 us at 140,190 tokens and 14 row blocks, 130 -> 116
-// at 13,679 and 7, and 76 -> 69 at 8,297; fp32 at d = 64 with one row block
+// per MFMA: 2209 -> 1772 us at 140,190 tokens and 14 row blocks, 80 -> 74 at
+// 8,297 and 7, and 114 -> 113 at 13,679; fp32 at d = 64 with one row block
 // (there a block of one wave) 39 -> 23 us, and its pass 2 44 -> 22.
 //
 // fp32 keys run v_mfma_f32_32x32x2f32 (64 cycles per 2 k): the matrix core

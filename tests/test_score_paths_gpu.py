@@ -82,8 +82,9 @@ def test_score_form(form):
 @pytest.mark.parametrize("form", [FORMS[0], FORMS[7], FORMS[8], FORMS[11], FORMS[12], FORMS[13]],
                          ids=["small", "aligned", "per-head", "persistent", "crossing", "f32"])
 def test_sums_beyond_the_reference(form):
-    """Logits that rise by more than 64 log2 units inside a block: its row
-    sums are redone against running maxima."""
+    """Logits that rise far above their block's reference: the row sums are
+    taken again against a higher one, or, where they are not finite, against
+    running maxima."""
     _run(*form, spike=24.0)
 
 
