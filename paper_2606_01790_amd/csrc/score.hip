@@ -106,6 +106,7 @@ int launch_score(const Geometry& g, const starkv_params& p, const void* q,
   SlabLaunch p1, p2;
   slab_launches(g.Lp, nlg, a.nrb, n_cu, a.n_chunks_max, a.n_out == 1,
                 a.n_out == 1 || a.W % 32 == 0, g.d, g.esz, &p1, &p2);
+  a.far = !p1.small;
 
   const int err = g.dtype == STARKV_BF16 ? run_score_bf16(a, g.d, p1, p2, st)
                                          : run_score_f32(a, g.d, p1, p2, st);

@@ -57,6 +57,7 @@ struct ScoreArgs {
   int64_t ls, gs, ts;   // element strides of the K cache
   int H, G, W, R, nrb, Lp;
   int n_chunks_max;
+  bool far;             // the records' references may lie far below their maxima
   float scale;          // log2(e) / sqrt(d)
   float2* part;         // [n_layers][G][n_chunks_max][nrb * 32]  (M, sum)
   float* sraw;          // [n_layers][Ns][Lp]
@@ -646,11 +647,14 @@ __global__ __launch_bounds__(kSlabThreads) void score_pass1(ScoreArgs a, SlabGri
 // merge_issue.
 constexpr int kMergeBatch = 8;
 // M + log2(l).  The logarithm is off by up to an ulp of its result, to one
-// side: taken of l, about 2^10 in ordinary calls and up to 2^32 under high
-// logits, that was most of S's error.  Of l's mantissa in [0.5, 1) it is off
-// by 2^-24 at most, and the sum is rounded once.  28 layers of 4 groups,
-// 2,915 tokens, S against 64 bits: 3.1e-7 and 6.3e-8; with a key 24 log2
-// units above the others in every group 3.6e-7 and 6.2e-8.
+// side.  Taken of l against the persistent pass 1's references, about 2^10 in
+// ordinary calls and up to 2^32 under high logits, that was most of S's
+// error; of l's mantissa in [0.5, 1) it is off by 2^-24 at most, and the sum
+// is rounded once.  28 layers of 4 groups, 2,915 tokens, S against 64 bits:
+// 3.1e-7 and 6.3e-8; with a key 24 log2 units above the others in every group
+// 3.6e-7 and 6.2e-8.  Not for the small pass 1 (exact maxima, at most 256
+// tokens a record, 1.7e-7): the statistics rank S, and a last bit that moves
+// may swap two ranks at a bin's edge, so those calls keep theirs.
 __device__ __forceinline__ float add_log2(float M, float l) {
   int e;
   const float m = frexpf(l, &e);
@@ -679,7 +683,8 @@ __device__ __forceinline__ float merge_row(const ScoreArgs& a, const float2* par
     if ((c0 += kMergeBatch) >= n_chunks) break;
     merge_issue(a, part, n_chunks, c0, r, p);
   }
-  return (r < a.R) ? add_log2(Mx, lx) : INFINITY;
+  if (r >= a.R) return INFINITY;
+  return a.far ? add_log2(Mx, lx) : Mx + log2f(lx);
 }
 
 // ---------------------------------------------------------------- pass 2
