@@ -188,7 +188,7 @@ __device__ __forceinline__ void stats_block(const StatsArgs& a, int* layer, int*
 enum KeyPlace {
   kInMemory,   // read from S in every pass
   kInLds,      // N <= kKeyCache
-  kFewInLds,   // N <= few_keys<NT>(): no histogram copies or cell table, short batches
+  kFewInLds,   // few of them: no histogram copies or cell table, short batches
 };
 template <int NT>
 constexpr int few_keys() {
@@ -1369,7 +1369,9 @@ void raise_lds_limits() {
 // histogram copies and the cell table cost a call of few keys more than they
 // save: us of the fused call with and without them, one layer of 4 groups,
 // 1,196 keys 30.5 / 29.0, 4,641 keys 35.2 / 33.8, 6,000 keys 37.9 / 35.8,
-// 7,700 keys 39.7 / 38.0; five spans of 1,196 keys 37.7 either way.
+// 7,700 keys 39.7 / 38.0; five spans of 1,196 keys 37.7 either way, six (27
+// layers of 2 groups, the update and the selection) 41.1 / 41.4: from five
+// spans on they are left out up to four keys per thread only.
 template <int NT, bool SEL, KeyPlace KEYS>
 void run_stats(const StatsArgs& a, const SelArgs& sel, hipStream_t st) {
   const int blocks = (stats_layer_blocks(a.G) + a.n_ent - 1) * a.n_layers;
@@ -1381,7 +1383,8 @@ int launch_stats(const StatsArgs& a, const SelArgs& sel, hipStream_t st) {
   raise_lds_limits();
   constexpr int kCache = StatsShape<NT>::kKeyCache;
   const int n = a.sp.off[a.sp.n];
-  if (n <= few_keys<NT>()) run_stats<NT, SEL, kFewInLds>(a, sel, st);
+  const int few = a.sp.n <= 4 || few_keys<NT>() == kCache ? few_keys<NT>() : 4 * NT;
+  if (n <= few) run_stats<NT, SEL, kFewInLds>(a, sel, st);
   else if (n > kCache) run_stats<NT, SEL, kInMemory>(a, sel, st);
   else if constexpr (few_keys<NT>() < kCache) run_stats<NT, SEL, kInLds>(a, sel, st);
   return (int)hipGetLastError();

@@ -388,7 +388,8 @@ def test_fused_binning_forms(form):
 # and of the few keys that are binned without histogram copies
 CACHE_EDGES = [
     (1, 64, 128, 0, False, 8, 8), (1, 3, 2731, 0, False, 8, 8), (2, 64, 64, 3, False, 16, 16),
-    (1, 64, 64, 0, True, 12, 8), (1, 17, 241, 0, True, 12, 8),
+    (1, 64, 64, 0, True, 12, 8), (1, 17, 241, 0, True, 12, 8), (4, 32, 64, 0, False, 8, 8),
+    (5, 32, 51, 0, False, 8, 8), (5, 21, 39, 0, False, 8, 8),
     (1, 128, 160, 0, False, 8, 8), (1, 3, 6827, 0, False, 8, 8), (1, 64, 96, 0, True, 12, 8),
     (1, 5, 1229, 0, True, 12, 8), (1, 32, 64, 0, True, 8, 8), (1, 3, 683, 0, True, 8, 8),
 ]
